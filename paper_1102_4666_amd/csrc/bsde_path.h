@@ -20,9 +20,9 @@
 
 namespace bsde {
 
-// The FP64 kernels' tables of sines, cosines and powers of two
-// (bsde_f64_math.h), one copy per workgroup, filled at the start of each
-// tile (run_tile).
+// The FP64 kernels' tables of logarithms, sines, cosines and powers of two
+// (bsde_f64_math.h), one copy per workgroup, filled when it starts
+// (fill_path_tables).
 static __shared__ f64::Tables f64_tables;
 
 // ---------------------------------------------------------------------------
@@ -79,9 +79,12 @@ struct Arith<double> {
     {
         return ((double)w + 0.5) * 0x1p-32;
     }
+    // v is kept above 2^-800 (it is zero for points at T, whose paths do not
+    // move: a normal of 2^-400 adds nothing to the state either), so that the
+    // radius' square root needs no case for zero
     static __device__ __forceinline__ double bm_scale(double v)
     {
-        return -2.0 * v;
+        return -2.0 * fmax(v, 0x1p-800);
     }
     // Box-Muller pair scaled by sqrt(v), scale = -2 v: R = sqrt(-2 v ln ua);
     // ln ua and the sine and cosine of the angle 2 pi ub from the words
@@ -91,7 +94,7 @@ struct Arith<double> {
                                                       double &n1, double = 0.0,
                                                       double = 0.0)
     {
-        double R = f64::sqrt_nonneg(scale * f64::log_word(wa));
+        double R = f64::sqrt_pos(scale * f64::log_word_tab(wa, f64_tables));
         double s, c;
         f64::sincos_turn_tab(wb, f64_tables, s, c);
         n0 = R * c;
@@ -149,23 +152,18 @@ __device__ __forceinline__ Real local_vol(Real level, Real level_a, Real lc,
 }
 
 // Coordinates of the Euler state.  With the bump volatility the paths carry
-// y = kappa (x - log c) -- kappa^2 = log2 e in FP32, 256 log2 e in FP64 at
-// d = 10, 1 in the other FP64 kernels -- so that the volatility costs a
-// square, one exponential and one fused multiply-add per asset and step:
-// level + (level a) 2^{-y^2} (FP32), level + (level a) 2^{-y^2/256} (FP64,
-// d = 10: the table exponential needs no reduction by ln 2), level +
-// (level a) e^{-y^2} (other FP64; there the scaled form saves nothing: the
-// vector instruction it takes off the volatility comes back as 64-bit
-// literal moves in the rest of the step).  Every increment of x is scaled
-// by kappa as well.  The other volatility kinds keep y = x.
-template <int VOL, typename Real, int D>
+// y = kappa (x - log c) -- kappa^2 = log2 e in FP32, 256 log2 e in FP64 --
+// so that the volatility costs a square, one exponential and one fused
+// multiply-add per asset and step: level + (level a) 2^{-y^2} (FP32), level +
+// (level a) 2^{-y^2/256} (FP64: the table exponential needs no reduction by
+// ln 2, and takes the square unrounded).  Every increment of x is scaled by
+// kappa as well.  The other volatility kinds keep y = x.
+template <int VOL, typename Real>
 struct EulerState {
     static constexpr bool kShift = VOL == kVolBump;
-    static constexpr bool kExp2F64 = kShift && sizeof(Real) == 8 && D >= 10;
-    static constexpr Real kappa =
-        !kShift ? Real(1)
-                : (sizeof(Real) == 4 ? Real(1.2011224087864498)
-                                     : (kExp2F64 ? Real(19.217958540583197) : Real(1)));
+    static constexpr Real kappa = !kShift ? Real(1)
+                                  : sizeof(Real) == 4 ? Real(1.2011224087864498)
+                                                      : Real(19.217958540583197);
     static __device__ __forceinline__ Real to(Real x, Real lc)
     {
         if constexpr (kShift) return (x - lc) * kappa;
@@ -182,10 +180,8 @@ struct EulerState {
         if constexpr (kShift) {
             if constexpr (sizeof(Real) == 4)
                 return fmaf(level_a, __builtin_amdgcn_exp2f(-y * y), level);
-            else if constexpr (kExp2F64)
-                return fma(level_a, f64::exp2_neg_tab(y * y, f64_tables), level);
             else
-                return fma(level_a, f64::exp_nonpos_tab(-y * y, f64_tables), level);
+                return fma(level_a, f64::exp2_neg_sq_tab(y, f64_tables), level);
         } else {
             return local_vol<VOL>(level, level_a, Real(0), spot, vt, y);
         }
@@ -330,6 +326,16 @@ __device__ __forceinline__ ConstAssets<Real> &reload_consts(uint64_t cbase)
     return *(ConstAssets<Real> *)a;
 }
 
+// The FP64 kernels' tables, copied once per workgroup before its first tile
+template <typename Real>
+__device__ __forceinline__ void fill_path_tables()
+{
+    if constexpr (sizeof(Real) == 8) {
+        f64::fill_tables(f64_tables, (int)threadIdx.x, kBlock);
+        __syncthreads();
+    }
+}
+
 // ---------------------------------------------------------------------------
 // The Monte Carlo path kernel.
 // Grid: n * groups workgroups of kBlock lanes; workgroup (i, g) runs the
@@ -355,6 +361,14 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
     constexpr int SG = (D % 4 == 0) ? 1 : ((D % 2 == 0) ? 2 : 4);
     constexpr int NB = SG * D / 4;
     constexpr int NBB = (D + 3) / 4; // bridge blocks
+    // Normals of a group of several blocks are made at the first step that
+    // needs them: later steps' normals do not wait in registers (the FP64
+    // d = 5 kernel keeps its Euler loop free of spills), and a path's last
+    // group makes no block beyond its last step.  Not at d = 10, two steps a
+    // group: at the FP64 kernel's two waves per SIMD the blocks made together
+    // hide each other's latencies (8192 points, M = 500, N = 50: 4.49 ms
+    // against 4.95), and the FP32 kernel would spill more.
+    constexpr bool kLateNormals = NB > 1 && D < 10;
     constexpr bool kXor3 = sizeof(Real) == 4 || D >= 2; // Philox XOR form
     // FP32 round keys in vector registers (16 of them): at d = 1, and at
     // d = 2 from eta = 5 on, where the kernel's own registers already hold
@@ -378,7 +392,7 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
     const Real h = (T - t0) / (Real)prm.N;
     // Euler state coordinates y = kappa (x - off); step normals come out of
     // Box-Muller already scaled by kappa sqrt(h)
-    using ES = EulerState<VOL, Real, D>;
+    using ES = EulerState<VOL, Real>;
     const Real step_scale = Arith<Real>::bm_scale(h * (ES::kappa * ES::kappa));
     const Real r = (Real)prm.r, omega = (Real)prm.omega, K = (Real)prm.K;
     const Real lc = (Real)prm.log_bump_c;
@@ -394,7 +408,10 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
     // address of prm in constant memory)
     constexpr bool kReloadConsts = RELOAD && sizeof(Real) == 8;
     const Real tscale = Real(2) / T;
-    const Real neg_half_hk = Real(-0.5) * ES::kappa * h;
+    Real neg_half_hk = Real(-0.5) * ES::kappa * h;
+    // (FP64 d = 3: opaque, so that its scalar operands are not kept beside
+    // it, which would overflow the scalar registers)
+    if constexpr (sizeof(Real) == 8 && D == 3) asm volatile("" : "+v"(neg_half_hk));
     const Real hk = ES::kappa * h;
     // The volatility levels as vector operands: the volatility's fused
     // multiply-add has another scalar operand (level a) already, and a
@@ -430,11 +447,6 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
     };
     __shared__ Rec rec[D][kBlock];
 
-    if constexpr (sizeof(Real) == 8) {
-        f64::fill_tables(f64_tables, (int)threadIdx.x, kBlock);
-        __syncthreads();
-    }
-
     // this lane's paths: count, mean and sum of squared deviations, updated
     // path by path (Welford), so the sum of squares never dwarfs the spread
     int cnt = 0;
@@ -464,19 +476,26 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
             // back from vector-register lanes with one vector instruction
             // per use
             Real G[4 * NB];
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
+            auto normals = [&](auto bc) {
+                constexpr int b = decltype(bc)::value;
                 const u32x4 w = block((uint32_t)m, (uint32_t)(grp * NB + b));
                 Arith<Real>::box_muller(w.x, w.y, step_scale, G[4 * b],
                                         G[4 * b + 1], c32, c33);
                 Arith<Real>::box_muller(w.z, w.w, step_scale, G[4 * b + 2],
                                         G[4 * b + 3], c32, c33);
-            }
+            };
+            if constexpr (!kLateNormals) static_for<NB>(normals);
             auto steps = [&](auto &acs) {
-#pragma unroll
-            for (int ss = 0; ss < SG; ++ss) {
+            static_for<SG>([&](auto sc) {
+                constexpr int ss = decltype(sc)::value;
                 const int s = grp * SG + ss;
                 if (s < prm.N) {
+                    // the blocks first needed by this step
+                    constexpr int b0 = (ss * D + 3) / 4, b1 = (ss * D + D + 3) / 4;
+                    if constexpr (kLateNormals)
+                        static_for<b1 - b0>([&](auto bc) {
+                            normals(std::integral_constant<int, b0 + decltype(bc)::value>{});
+                        });
                     if (s == jstar) {
 #pragma unroll
                         for (int j = 0; j < D; ++j)
@@ -503,7 +522,7 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
                         else X[j] = fma(acs.drift[j], hk, inner);
                     }
                 }
-            }
+            });
             };
             if constexpr (kReloadConsts) steps(reload_consts<Real>(cbase));
             else steps(ac);
@@ -824,6 +843,7 @@ __global__ __launch_bounds__(kBlock, (min_waves<D, Real>())) void path_kernel(
 {
     const int i = blockIdx.x / prm.groups;
     const int g = blockIdx.x - i * prm.groups;
+    fill_path_tables<Real>();
     // prm is the first kernel argument: its copy at the start of the
     // kernel-argument segment is the one the scalar loads read
     run_tile<D, ETA, Real, VOL, Q, const Real *__restrict__, OP, true>(
@@ -844,6 +864,7 @@ __global__ __launch_bounds__(kBlock, (min_waves<D, Real>())) void batch_path_ker
 {
     __shared__ long long next;
     const long long total = tile_begin[nprob];
+    fill_path_tables<Real>();
     for (;;) {
         if (threadIdx.x == 0) next = (long long)atomicAdd(counter, 1u);
         __syncthreads();
