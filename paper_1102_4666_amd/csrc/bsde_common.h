@@ -29,9 +29,11 @@ __host__ __device__ __forceinline__ void static_for(F &&f)
 
 constexpr int kMaxD = 10;
 constexpr int kBlock = 256; // lanes per workgroup of the path kernel
-// largest basis whose set-up factorisations run on the device (two
-// kSmallFactorP^2 FP64 matrices in the LDS of one wave's workgroup)
-constexpr int kSmallFactorP = 56;
+// largest padded basis whose set-up factorisations run in one workgroup with
+// the matrices in LDS, and the most 16-column tiles of any basis (448
+// functions; the largest set built has 386)
+constexpr int kSmallFactorP = 64;
+constexpr int kFactorTiles = 28;
 
 // ---------------------------------------------------------------------------
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11).  Counter words:

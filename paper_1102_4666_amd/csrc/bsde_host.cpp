@@ -14,15 +14,14 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <chrono>
 #include <cmath>
 #include <tuple>
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
-#include <thread>
 #include <vector>
 
 namespace bsde {
@@ -53,18 +52,18 @@ hipError_t launch_batch_channels(int nprob, int max_cb, hipStream_t s,
                                  const BatchUpdateDesc *d);
 hipError_t launch_reset_counters(unsigned int *c, int n, hipStream_t s);
 hipError_t launch_basis_matrix(const double *pts, int n, int ld, int dp,
-                               const int8_t *nu, int pa, int pap,
+                               const int8_t *nu, int pa, int pap, int eta,
                                const double *mid, const double *scale,
                                double T, double *B, hipStream_t s);
 hipError_t launch_gram(const double *A, int ld, int pap, int rows_per_chunk,
                        int chunks, const int2 *pairs, int npairs,
                        double *partial, int pa, double *G, hipStream_t s);
-hipError_t launch_gemm_ax(const double *A, int ld, const double *X, int pap,
+hipError_t launch_gemm_ax(const double *A, int ld, const double *X, int pap, bool upper,
                           double *Y, int ldy, int nrows, const int *colmap,
-                          int ncols, hipStream_t s, const int *skip = nullptr);
-hipError_t launch_small_factor(const double *G, int pa, int pap, double rel_tol,
-                               int stage, double *X1, double *Xp, int *status,
-                               hipStream_t s);
+                          int ncols, hipStream_t s, const int *skip);
+size_t factor_workspace(int pap);
+hipError_t launch_factor(const double *G, int pa, int pap, double rel_tol, int stage,
+                         double *X1, double *Xp, double *work, int *status, hipStream_t s);
 bool kernel_op_exists(int d, int vol);
 hipError_t launch_kernel_path(int d, bool fp32, int blocks, hipStream_t s,
                               const PathParams &prm, const double *pts,
@@ -275,28 +274,6 @@ static double cheb_deriv_coef(int a, int b)
     return b == 0 ? (double)a : 2.0 * a;
 }
 
-// Runs fn(begin, end) over [0, count) split across up to 16 host threads;
-// work is the number of multiply-adds of the whole loop, and loops below
-// 2^20 of them run in the calling thread.
-template <typename F>
-static void parallel_for(long count, long min_chunk, double work, F fn)
-{
-    const long hw = std::max(1u, std::thread::hardware_concurrency());
-    long nt = std::max(1L, std::min({16L, hw, count / std::max(1L, min_chunk)}));
-    if (work < (double)(1 << 20)) nt = 1;
-    if (nt <= 1) {
-        fn(0L, count);
-        return;
-    }
-    std::vector<std::thread> th;
-    const long per = (count + nt - 1) / nt;
-    for (long t = 0; t < nt; ++t) {
-        const long b = t * per, e = std::min(count, b + per);
-        if (b < e) th.emplace_back(fn, b, e);
-    }
-    for (auto &x : th) x.join();
-}
-
 // q in tenths when a kernel of that hyperbolic set is built for (d, eta),
 // else 10 (the total-degree kernel, used with a mask for q < 1)
 static int kernel_q10(int d, int eta, double q)
@@ -305,54 +282,6 @@ static int kernel_q10(int d, int eta, double q)
     const int r = (int)std::lround(q10);
     if (r >= 1 && r < 10 && std::fabs(q10 - r) < 1e-9 && kernel_exists(d, eta, r)) return r;
     return 10;
-}
-
-// Upper Cholesky factor R of a symmetric positive definite G (p x p,
-// row-major): G = R'R.  Right-looking; false when a pivot is not positive
-// or falls below rel_tol times the largest diagonal entry of R.
-static bool chol_upper(const std::vector<double> &G, int p, double rel_tol,
-                       std::vector<double> &R)
-{
-    R = G;
-    double dmax = 0.0;
-    for (int j = 0; j < p; ++j) dmax = std::max(dmax, G[(size_t)j * p + j]);
-    dmax = std::sqrt(std::max(dmax, 0.0));
-    for (int j = 0; j < p; ++j) {
-        double *rj = &R[(size_t)j * p];
-        const double piv = rj[j];
-        if (!(piv > 0.0) || !(std::sqrt(piv) > rel_tol * dmax)) return false;
-        const double r = std::sqrt(piv);
-        for (int c = j; c < p; ++c) rj[c] /= r;
-        // trailing update of the upper triangle, rows independent
-        parallel_for(p - j - 1, 8, 0.5 * (double)(p - j) * (p - j),
-                     [&, j, rj](long b, long e) {
-            for (long rr = j + 1 + b; rr < j + 1 + e; ++rr) {
-                double *row = &R[(size_t)rr * p];
-                const double f = rj[rr];
-                for (int c = (int)rr; c < p; ++c) row[c] -= f * rj[c];
-            }
-        });
-    }
-    for (int r = 1; r < p; ++r)
-        for (int c = 0; c < r; ++c) R[(size_t)r * p + c] = 0.0;
-    return true;
-}
-
-// Inverse of an upper triangular R (p x p, row-major), column by column
-static std::vector<double> tri_inv_upper(const std::vector<double> &R, int p)
-{
-    std::vector<double> X((size_t)p * p, 0.0);
-    parallel_for(p, 8, (double)p * p * p / 6, [&](long b, long e) {
-        for (long c = b; c < e; ++c) {
-            X[(size_t)c * p + c] = 1.0 / R[(size_t)c * p + c];
-            for (long r = c - 1; r >= 0; --r) {
-                double s = 0.0;
-                for (long k = r + 1; k <= c; ++k) s += R[(size_t)r * p + k] * X[(size_t)k * p + c];
-                X[(size_t)r * p + c] = -s / R[(size_t)r * p + r];
-            }
-        }
-    });
-    return X;
 }
 
 // Set-up streams (non-blocking, one per concurrent set-up, reused)
@@ -440,7 +369,9 @@ static void make_points(const bsde_problem_s *h, int k, std::vector<double> &pts
 // 64 x 64 block pairs, at least 256 rows each)
 static void setup_shape(int n, int pap, int &ld, int &rpc, int &chunks)
 {
-    ld = (n + 63) & ~63;
+    // an odd multiple of 64 rows: columns a power of two of rows apart would
+    // fall on the same memory channels
+    ld = (((n + 63) / 64) | 1) * 64;
     const int nb = (pap + 63) / 64;
     // about 2048 single-wave workgroups over the block pairs and chunks,
     // at least 64 rows a chunk (a chunk's loads are a dependent chain, so
@@ -483,184 +414,209 @@ static void pinned_put(void *p, size_t cap)
 }
 
 // Pseudo-inverse W = B^+ (p x n, row-major; rows of inactive multi-indices
-// zero) of the basis matrix of the grid by CholeskyQR2 on the device:
-// B (n x pa) is formed from the device copy of the points, the Gram
-// matrices and the tall-skinny products run on the device; the two pa x pa
-// Cholesky factorisations and triangular inverses run on the device too
-// when pa <= kSmallFactorP (one wave, LDS), else on the host.  Returns
-// BSDE_ERANK when B is numerically rank deficient (a Cholesky pivot of B'B
-// below 1e-7 of the largest, i.e. a condition number beyond ~1e7).
-// Stream-ordered on s (the points must be uploaded on s or before); the
-// call synchronizes s.
-static bsde_status device_pseudo_inverse(bsde_problem_s *h, const std::vector<int> &act,
-                                         hipStream_t s)
-{
-    const int n = h->n, pa = (int)act.size(), pap = pad16(pa), dp = h->d + 1;
-    std::vector<int2> pairs;
-    const int nb = (pap + 63) / 64;
-    for (int bi = 0; bi < nb; ++bi)
-        for (int bj = bi; bj < nb; ++bj) pairs.push_back(make_int2(bi, bj));
-    int ld, rpc, chunks;
-    setup_shape(n, pap, ld, rpc, chunks);
-    std::vector<int8_t> nu_act((size_t)pa * dp);
-    for (int c = 0; c < pa; ++c)
-        std::memcpy(&nu_act[(size_t)c * dp], &h->nu[(size_t)act[c] * dp], dp);
-    std::vector<double> ms(2 * kMaxD, 0.0);
-    for (int j = 0; j < h->d; ++j) {
-        ms[j] = h->base.mid[j];
-        ms[kMaxD + j] = h->base.scale[j];
+// zero) of the basis matrix of the grid by CholeskyQR2 on the device: the
+// basis matrix from the device copy of the points, the Gram matrices, the
+// factorisations and the products.  init allocates the workspace and uploads
+// the small inputs, enqueue runs everything stream-ordered on s (the points
+// must be uploaded on s or before) and ends with the copy of the status to
+// host memory: 0, or not when B is numerically rank deficient (a Cholesky
+// pivot of B'B below 1e-7 of the largest, i.e. a condition number beyond
+// ~1e7); W is then left as it was.  The workspace goes back to the pool with
+// the object, so s must be synchronized before.
+namespace {
+class PseudoInverse {
+public:
+    explicit PseudoInverse(const bsde_problem_s *h) : h_(h) {}
+    PseudoInverse(const PseudoInverse &) = delete;
+    PseudoInverse &operator=(const PseudoInverse &) = delete;
+    ~PseudoInverse()
+    {
+        for (void *q : {(void *)dB_, (void *)dQ_, (void *)dPart_, (void *)dG_, (void *)dSmall_})
+            pool_free(q);
+        if (stage_pageable_.empty()) pinned_put(stage_, pin_cap_);
     }
 
-    // the small inputs of the set-up kernels travel in one upload:
-    // index set | domain map | Gram block pairs | active columns | status
-    auto al8 = [](size_t b) { return (b + 7) & ~(size_t)7; };
-    const size_t o_ms = al8(nu_act.size()), o_pairs = o_ms + sizeof(double) * ms.size(),
-                 o_map = o_pairs + sizeof(int2) * pairs.size(),
-                 o_status = al8(o_map + sizeof(int) * pa), n_small = o_status + 8;
-    size_t pin_cap = 0;
-    unsigned char *stage = (unsigned char *)pinned_get(n_small, &pin_cap);
-    std::vector<unsigned char> stage_pageable;
-    if (!stage) {
-        stage_pageable.resize(n_small);
-        stage = stage_pageable.data();
-    }
-    std::memset(stage, 0, n_small);
-    std::memcpy(stage, nu_act.data(), nu_act.size());
-    std::memcpy(stage + o_ms, ms.data(), sizeof(double) * ms.size());
-    std::memcpy(stage + o_pairs, pairs.data(), sizeof(int2) * pairs.size());
-    std::memcpy(stage + o_map, act.data(), sizeof(int) * pa);
-    const bool small = pa <= kSmallFactorP;
+    hipError_t init(hipStream_t s)
+    {
+        const std::vector<int> &act = h_->act;
+        const int dp = h_->d + 1;
+        pa_ = (int)act.size();
+        pap_ = pad16(pa_);
+        setup_shape(h_->n, pap_, ld_, rpc_, chunks_);
+        std::vector<int2> pairs;
+        const int nb = (pap_ + 63) / 64;
+        for (int bi = 0; bi < nb; ++bi)
+            for (int bj = bi; bj < nb; ++bj) pairs.push_back(make_int2(bi, bj));
+        npairs_ = (int)pairs.size();
+        // the small inputs of the set-up kernels travel in one upload:
+        // index set | domain map | Gram block pairs | active columns | status
+        auto al8 = [](size_t b) { return (b + 7) & ~(size_t)7; };
+        o_ms_ = al8((size_t)pa_ * dp);
+        o_pairs_ = o_ms_ + sizeof(double) * 2 * kMaxD;
+        o_map_ = o_pairs_ + sizeof(int2) * pairs.size();
+        o_status_ = al8(o_map_ + sizeof(int) * pa_);
+        const size_t n_small = o_status_ + 8;
+        stage_ = (unsigned char *)pinned_get(n_small, &pin_cap_);
+        if (!stage_) {
+            stage_pageable_.resize(n_small);
+            stage_ = stage_pageable_.data();
+        }
+        std::memset(stage_, 0, n_small);
+        for (int c = 0; c < pa_; ++c)
+            std::memcpy(stage_ + (size_t)c * dp, &h_->nu[(size_t)act[c] * dp], dp);
+        std::memcpy(stage_ + o_ms_, h_->base.mid, sizeof(double) * h_->d);
+        std::memcpy(stage_ + o_ms_ + sizeof(double) * kMaxD, h_->base.scale,
+                    sizeof(double) * h_->d);
+        std::memcpy(stage_ + o_pairs_, pairs.data(), sizeof(int2) * pairs.size());
+        std::memcpy(stage_ + o_map_, act.data(), sizeof(int) * pa_);
 
-    double *dB = nullptr, *dQ = nullptr, *dPart = nullptr, *dG = nullptr,
-           *dX = nullptr, *dX1 = nullptr;
-    unsigned char *dSmall = nullptr;
-    bsde_status st = BSDE_OK;
-    std::string why;
-    auto chk = [&](hipError_t e, const char *what) {
-        if (e == hipSuccess || st != BSDE_OK) return st == BSDE_OK;
-        st = e == hipErrorOutOfMemory ? BSDE_ENOMEM : BSDE_EDEVICE;
-        why = std::string(what) + ": " + hipGetErrorString(e);
-        return false;
-    };
-    std::vector<double> G((size_t)pa * pa), R1, R2;
-    do {
-        if (!chk(pool_alloc((void **)&dB, sizeof(double) * ld * pap), "device allocation") ||
-            !chk(pool_alloc((void **)&dQ, sizeof(double) * ld * pap), "device allocation") ||
-            !chk(pool_alloc((void **)&dPart, sizeof(double) * chunks * pap * pap), "device allocation") ||
-            !chk(pool_alloc((void **)&dG, sizeof(double) * pa * pa), "device allocation") ||
-            !chk(pool_alloc((void **)&dX, sizeof(double) * pap * pap), "device allocation") ||
-            !chk(pool_alloc((void **)&dSmall, n_small), "device allocation") ||
-            (small && !chk(pool_alloc((void **)&dX1, sizeof(double) * pa * pa), "device allocation")))
-            break;
-        if (!chk(hipMemcpyAsync(dSmall, stage, n_small, hipMemcpyHostToDevice, s), "upload"))
-            break;
-        const int8_t *dNu = (const int8_t *)dSmall;
-        const double *dMS = (const double *)(dSmall + o_ms);
-        const int2 *dPairs = (const int2 *)(dSmall + o_pairs);
-        const int *dMap = (const int *)(dSmall + o_map);
-        int *dStatus = (int *)(dSmall + o_status);
-        if (small) {
-            // CholeskyQR2 with the p x p steps on the device: stream-ordered,
-            // one synchronisation (the status) at the end; the last product
-            // leaves W untouched when a rank test failed
-            int status = 0;
-            if (!chk(launch_basis_matrix(h->d_pts, n, ld, dp, dNu, pa, pap, dMS, dMS + kMaxD,
-                                         h->base.T, dB, s), "basis kernel") ||
-                !chk(launch_gram(dB, ld, pap, rpc, chunks, dPairs, (int)pairs.size(), dPart, pa,
-                                 dG, s), "gram kernel") ||
-                !chk(launch_small_factor(dG, pa, pap, 1e-7, 1, dX1, dX, dStatus, s),
-                     "factor kernel") ||
-                !chk(launch_gemm_ax(dB, ld, dX, pap, dQ, ld, ld, nullptr, pap, s, dStatus),
-                     "gemm kernel") ||
-                !chk(launch_gram(dQ, ld, pap, rpc, chunks, dPairs, (int)pairs.size(), dPart, pa,
-                                 dG, s), "gram kernel") ||
-                !chk(launch_small_factor(dG, pa, pap, 1e-3, 2, dX1, dX, dStatus, s),
-                     "factor kernel"))
-                break;
-            if (pa < h->p &&
-                !chk(hipMemsetAsync(h->d_W, 0, sizeof(double) * (size_t)h->p * n, s), "memset"))
-                break;
-            if (!chk(launch_gemm_ax(dQ, ld, dX, pap, h->d_W, n, n, dMap, pa, s, dStatus),
-                     "gemm kernel") ||
-                !chk(hipMemcpyAsync(&status, dStatus, sizeof(int), hipMemcpyDeviceToHost, s),
-                     "download") ||
-                !chk(hipStreamSynchronize(s), "set-up"))
-                break;
-            if (status != 0) {
-                st = BSDE_ERANK;
-                why = "basis matrix is numerically rank deficient on the grid";
+        // two p x n point matrices, the Gram partials, and the p x p matrices
+        // (G, the two right factors and the factorisation's own) in one block
+        const size_t sq = (size_t)pap_ * pap_;
+        hipError_t e = pool_alloc((void **)&dB_, sizeof(double) * ld_ * pap_);
+        if (e == hipSuccess) e = pool_alloc((void **)&dQ_, sizeof(double) * ld_ * pap_);
+        if (e == hipSuccess) e = pool_alloc((void **)&dPart_, sizeof(double) * chunks_ * sq);
+        if (e == hipSuccess)
+            e = pool_alloc((void **)&dG_, sizeof(double) * (3 * sq + factor_workspace(pap_)));
+        if (e == hipSuccess) e = pool_alloc((void **)&dSmall_, n_small);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(dSmall_, stage_, n_small, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess && pa_ < h_->p)
+            e = hipMemsetAsync(h_->d_W, 0, sizeof(double) * (size_t)h_->p * h_->n, s);
+        return e;
+    }
+
+    hipError_t enqueue(hipStream_t s, int *status)
+    {
+        const int n = h_->n;
+        const size_t sq = (size_t)pap_ * pap_;
+        double *dX1 = dG_ + sq, *dX = dG_ + 2 * sq, *dWork = dG_ + 3 * sq;
+        const double *dMS = (const double *)(dSmall_ + o_ms_);
+        const int2 *dPairs = (const int2 *)(dSmall_ + o_pairs_);
+        int *dStatus = (int *)(dSmall_ + o_status_);
+        hipError_t e = launch_basis_matrix(h_->d_pts, n, ld_, h_->d + 1, (const int8_t *)dSmall_,
+                                           pa_, pap_, h_->eta, dMS, dMS + kMaxD, h_->base.T, dB_,
+                                           s);
+        if (e == hipSuccess)
+            e = launch_gram(dB_, ld_, pap_, rpc_, chunks_, dPairs, npairs_, dPart_, pa_, dG_, s);
+        // a failed rank test leaves its status, and the later steps do nothing
+        if (e == hipSuccess) e = launch_factor(dG_, pa_, pap_, 1e-7, 1, dX1, dX, dWork, dStatus, s);
+        if (e == hipSuccess)
+            e = launch_gemm_ax(dB_, ld_, dX1, pap_, true, dQ_, ld_, ld_, nullptr, pap_, s, dStatus);
+        if (e == hipSuccess)
+            e = launch_gram(dQ_, ld_, pap_, rpc_, chunks_, dPairs, npairs_, dPart_, pa_, dG_, s);
+        if (e == hipSuccess) e = launch_factor(dG_, pa_, pap_, 1e-3, 2, dX1, dX, dWork, dStatus, s);
+        if (e == hipSuccess)
+            e = launch_gemm_ax(dQ_, ld_, dX, pap_, false, h_->d_W, n, n,
+                               (const int *)(dSmall_ + o_map_), pa_, s, dStatus);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(status, dStatus, sizeof(int), hipMemcpyDeviceToHost, s);
+        return e;
+    }
+
+    // host memory of the object for one status
+    int *own_status() { return (int *)(stage_ + o_status_); }
+
+private:
+    const bsde_problem_s *h_;
+    int pa_ = 0, pap_ = 0, ld_ = 0, rpc_ = 0, chunks_ = 0, npairs_ = 0;
+    size_t o_ms_ = 0, o_pairs_ = 0, o_map_ = 0, o_status_ = 0, pin_cap_ = 0;
+    unsigned char *stage_ = nullptr, *dSmall_ = nullptr;
+    std::vector<unsigned char> stage_pageable_;
+    double *dB_ = nullptr, *dQ_ = nullptr, *dPart_ = nullptr, *dG_ = nullptr;
+};
+constexpr const char *kRankMessage = "basis matrix is numerically rank deficient on the grid";
+} // namespace
+
+// The redrawn points of one solve on stream s (Algorithm 1): draw(h, k) sends
+// iteration k's points up from one of two pinned slots and forms their
+// pseudo-inverse, all stream-ordered, so that the host draws the next
+// iteration's points while the GPU works; full_rank looks at the rank tests
+// once s is synchronized.
+namespace {
+class RedrawWork {
+public:
+    explicit RedrawWork(hipStream_t s) : s_(s) {}
+    RedrawWork(const RedrawWork &) = delete;
+    RedrawWork &operator=(const RedrawWork &) = delete;
+    ~RedrawWork()
+    {
+        if (!pinv_) return;
+        (void)hipStreamSynchronize(s_); // also after an error: the buffers go back
+        for (Slot &q : slot_) {
+            pinned_put(q.mem, q.cap);
+            if (q.sent) event_put(q.sent);
+        }
+        pinned_put(pinned_status_, status_cap_);
+    }
+
+    hipError_t draw(bsde_problem_s *h, int k)
+    {
+        const size_t bytes = sizeof(double) * h->pts.size();
+        hipError_t e = hipSuccess;
+        if (!pinv_) {
+            pinv_.reset(new PseudoInverse(h));
+            status_.assign((size_t)h->K_it, 0);
+            for (Slot &q : slot_) {
+                // (too large to pin: the points then go up from h->pts)
+                if (bytes <= kPinnedMax) q.mem = pinned_get(bytes, &q.cap);
+                if ((e = event_get(&q.sent)) != hipSuccess) return e;
             }
-            break;
+            if ((e = pinv_->init(s_)) != hipSuccess) return e;
+            pinned_status_ = (int *)pinned_get(sizeof(int) * status_.size(), &status_cap_);
         }
-        // B and G1 = B'B
-        if (!chk(launch_basis_matrix(h->d_pts, n, ld, dp, dNu, pa, pap, dMS, dMS + kMaxD,
-                                     h->base.T, dB, s), "basis kernel") ||
-            !chk(launch_gram(dB, ld, pap, rpc, chunks, dPairs, (int)pairs.size(), dPart, pa, dG, s),
-                 "gram kernel") ||
-            !chk(hipMemcpyAsync(G.data(), dG, sizeof(double) * G.size(), hipMemcpyDeviceToHost, s),
-                 "download") ||
-            !chk(hipStreamSynchronize(s), "set-up"))
-            break;
-        if (!chol_upper(G, pa, 1e-7, R1)) {
-            st = BSDE_ERANK;
-            why = "basis matrix is numerically rank deficient on the grid";
-            break;
-        }
-        // Q1 = B R1^{-1} (all pap columns: the padding comes out zero)
-        const std::vector<double> X1 = tri_inv_upper(R1, pa);
-        std::vector<double> Xp((size_t)pap * pap, 0.0);
-        for (int r = 0; r < pa; ++r)
-            std::memcpy(&Xp[(size_t)r * pap], &X1[(size_t)r * pa], sizeof(double) * pa);
-        if (!chk(hipMemcpyAsync(dX, Xp.data(), sizeof(double) * Xp.size(), hipMemcpyHostToDevice, s),
-                 "upload") ||
-            !chk(launch_gemm_ax(dB, ld, dX, pap, dQ, ld, ld, nullptr, pap, s), "gemm kernel") ||
-            !chk(launch_gram(dQ, ld, pap, rpc, chunks, dPairs, (int)pairs.size(), dPart, pa, dG, s),
-                 "gram kernel") ||
-            !chk(hipMemcpyAsync(G.data(), dG, sizeof(double) * G.size(), hipMemcpyDeviceToHost, s),
-                 "download") ||
-            !chk(hipStreamSynchronize(s), "set-up"))
-            break;
-        if (!chol_upper(G, pa, 1e-3, R2)) {
-            st = BSDE_ERANK;
-            why = "basis matrix is numerically rank deficient on the grid";
-            break;
-        }
-        // B^+' = Q1 P with P = R2^{-1} R2^{-T} R1^{-T}
-        const std::vector<double> Y2 = tri_inv_upper(R2, pa);
-        std::vector<double> T2((size_t)pa * pa, 0.0); // R2^{-1} R2^{-T}
-        parallel_for(pa, 8, (double)pa * pa * pa / 3, [&](long b, long e) {
-            for (long r = b; r < e; ++r)
-                for (int c = 0; c < pa; ++c) {
-                    double v = 0.0;
-                    for (int k = (int)std::max<long>(r, c); k < pa; ++k)
-                        v += Y2[(size_t)r * pa + k] * Y2[(size_t)c * pa + k];
-                    T2[(size_t)r * pa + c] = v;
-                }
-        });
-        std::fill(Xp.begin(), Xp.end(), 0.0);
-        parallel_for(pa, 8, (double)pa * pa * pa / 2, [&](long b, long e) {
-            for (long r = b; r < e; ++r)
-                for (int c = 0; c < pa; ++c) {
-                    double v = 0.0; // sum_k T2[r][k] X1[c][k], X1 upper
-                    for (int k = c; k < pa; ++k) v += T2[(size_t)r * pa + k] * X1[(size_t)c * pa + k];
-                    Xp[(size_t)r * pap + c] = v;
-                }
-        });
-        if (pa < h->p &&
-            !chk(hipMemsetAsync(h->d_W, 0, sizeof(double) * (size_t)h->p * n, s), "memset"))
-            break;
-        if (!chk(hipMemcpyAsync(dX, Xp.data(), sizeof(double) * Xp.size(), hipMemcpyHostToDevice, s),
-                 "upload") ||
-            !chk(launch_gemm_ax(dQ, ld, dX, pap, h->d_W, n, n, dMap, pa, s), "gemm kernel") ||
-            !chk(hipStreamSynchronize(s), "set-up"))
-            break;
-    } while (false);
-    if (st != BSDE_OK) (void)hipStreamSynchronize(s);
-    if (stage_pageable.empty()) pinned_put(stage, pin_cap);
-    for (void *q : {(void *)dB, (void *)dQ, (void *)dPart, (void *)dG, (void *)dX,
-                    (void *)dX1, (void *)dSmall})
-        pool_free(q);
-    if (st != BSDE_OK) return fail(st, why);
+        Slot &q = slot_[count_ & 1];
+        if (!q.mem) e = hipStreamSynchronize(s_); // h->pts is still being read
+        else if (count_ >= 2) e = hipEventSynchronize(q.sent);
+        if (e != hipSuccess) return e;
+        make_points(h, k, h->pts);
+        if (q.mem) std::memcpy(q.mem, h->pts.data(), bytes);
+        e = hipMemcpyAsync(h->d_pts, q.mem ? q.mem : (void *)h->pts.data(), bytes,
+                           hipMemcpyHostToDevice, s_);
+        if (e == hipSuccess) e = hipEventRecord(q.sent, s_);
+        if (e == hipSuccess) e = pinv_->enqueue(s_, status() + count_);
+        if (e != hipSuccess) return e;
+        ++count_;
+        h->pts_k = k;
+        return hipSuccess;
+    }
+
+    bool full_rank()
+    {
+        for (int i = 0; i < count_; ++i)
+            if (status()[i] != 0) return false;
+        return true;
+    }
+
+private:
+    int *status() { return pinned_status_ ? pinned_status_ : status_.data(); }
+    struct Slot {
+        void *mem = nullptr;
+        size_t cap = 0;
+        hipEvent_t sent = nullptr;
+    };
+    hipStream_t s_;
+    std::unique_ptr<PseudoInverse> pinv_;
+    Slot slot_[2];
+    int *pinned_status_ = nullptr;
+    std::vector<int> status_;
+    size_t status_cap_ = 0;
+    int count_ = 0;
+};
+} // namespace
+
+// The pseudo-inverse of the problem's points; synchronizes s
+static bsde_status device_pseudo_inverse(const bsde_problem_s *h, hipStream_t s)
+{
+    PseudoInverse pinv(h);
+    hipError_t e = pinv.init(s);
+    if (e == hipSuccess) e = pinv.enqueue(s, pinv.own_status());
+    const hipError_t se = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = se;
+    if (e != hipSuccess)
+        return fail(e == hipErrorOutOfMemory ? BSDE_ENOMEM : BSDE_EDEVICE,
+                    std::string("least-squares set-up: ") + hipGetErrorString(e));
+    if (*pinv.own_status() != 0) return fail(BSDE_ERANK, kRankMessage);
     return BSDE_OK;
 }
 
@@ -1105,7 +1061,7 @@ bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
     // (the kernel operator fits nothing: only the upload to wait for)
     bsde_status pst = BSDE_OK;
     if (!kop) {
-        pst = device_pseudo_inverse(h, act, us);
+        pst = device_pseudo_inverse(h, us);
     } else {
         const hipError_t se = hipStreamSynchronize(us);
         if (se != hipSuccess)
@@ -1213,7 +1169,7 @@ bsde_status bsde_solve(bsde_problem h, void *hip_stream)
         std::vector<hipEvent_t> &v;
         ~Release() { for (auto &x : v) event_put(x); }
     } release_events{ev};
-    double t_setup = 0.0;
+    RedrawWork redraw(s);
     HIP_TRY(hipEventRecord(ev[0], s));
     // channel table of the starting coefficients (the kernel operator's
     // table already holds the current point values)
@@ -1225,18 +1181,14 @@ bsde_status bsde_solve(bsde_problem h, void *hip_stream)
         hipEvent_t *e = per ? &ev[2 + (size_t)per * it] : nullptr;
         if (h->redraw && h->pts_k != k) {
             // Algorithm 1: new points for this iteration, and the
-            // pseudo-inverse of their basis matrix (after the previous
-            // iteration is done with the old ones)
-            HIP_TRY(hipStreamSynchronize(s));
-            const auto t0 = std::chrono::steady_clock::now();
-            make_points(h, k, h->pts);
-            HIP_TRY(hipMemcpyAsync(h->d_pts, h->pts.data(), sizeof(double) * h->pts.size(),
-                                   hipMemcpyHostToDevice, s));
-            const bsde_status pst = device_pseudo_inverse(h, h->act, s);
-            if (pst != BSDE_OK) return pst;
-            h->pts_k = k;
-            t_setup += std::chrono::duration<double, std::milli>(
-                           std::chrono::steady_clock::now() - t0).count();
+            // pseudo-inverse of their basis matrix (stream-ordered after the
+            // previous iteration's use of the old ones)
+            const hipError_t re = redraw.draw(h, k);
+            if (re != hipSuccess) {
+                h->pts_k = -1; // the points on the device are not known
+                return fail(re == hipErrorOutOfMemory ? BSDE_ENOMEM : BSDE_EDEVICE,
+                            std::string("redrawn points: ") + hipGetErrorString(re));
+            }
         }
         PathParams prm = h->base;
         prm.k = (uint32_t)k;
@@ -1290,10 +1242,13 @@ bsde_status bsde_solve(bsde_problem h, void *hip_stream)
     }
     float tot;
     hipEventElapsedTime(&tot, ev[0], ev[1]);
-    (void)t_setup; // included in the total (host-side set-up between launches)
     HIP_TRY(hipMemcpyAsync(h->alpha_hist.data(), h->d_alpha,
                            sizeof(double) * h->alpha_hist.size(), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    if (!redraw.full_rank()) {
+        h->pts_k = -1;
+        return fail(BSDE_ERANK, kRankMessage);
+    }
     if (iters > 0) {
         h->timings[0] = t_path / iters;
         h->timings[1] = t_fin / iters;
