@@ -363,6 +363,76 @@ struct ChannelRows {
 };
 
 // ---------------------------------------------------------------------------
+// The cubic form of u: over an index set whose multi-indices are of total
+// degree at most 3 or, up to degree 5, of one variate alone (the total-degree
+// set of degree 3, and the hyperbolic sets of eq. hyper_set at d = 10) u is a
+// cubic polynomial in the d + 1 mapped variates z plus c_4v z_v^4 + c_5v z_v^5
+// for each.  The cubic's Hessian is affine,
+//   H_vw(z) = H0_vw + sum_k C_vwk z_k,
+// and with q = H(z) z, G_v = g_v + (H0 z)_v / 2 (g the gradient at z = 0) and
+// L = u(0) + g z / 3 its gradient and value are
+//   d_v u = G_v + q_v / 2,   u = L + z (2 G / 3 + q / 6)
+// (the cubic Taylor expansion at 0).  u, d_t u, grad u and grad^2 u then cost
+// one affine row per entry of the Hessian, of G and L and two products per
+// Hessian entry: 936 + 242 products at d = 10 instead of the 1,882 of the
+// derivative channels of the basis functions and the ~550 that form those.
+// u(T, x) is a cubic in the d spatial variates alone (z_0 = 1 there).
+//
+// The table of a problem holds the rows' coefficients, constant first, then
+// z_0 .. z_d (ka = d + 2 of them): the Hessian pairs v <= w (row-major upper
+// triangle), G_0 .. G_d, L.  FP32 paths take the rows four at a time on the
+// matrix cores: coefficient k of row 4 g + r at (g ka + k) 4 + r, and u(T, x)
+// by rows too (kt = d + 1 coefficients; pair j <= k of x M(x) x with M = H0/2 +
+// C x / 6, off-diagonal pairs doubled, then u + g x) at off_t.  FP64 paths
+// take row after row, and u(T, x) nested, at off_t: the constant, then for
+// each j: g_j, for each k >= j: h_jk, for each l >= k: c_jkl (coefficients of
+// the monomials).  c_4v, c_5v of every variate, when there are any, at off_q.
+// ---------------------------------------------------------------------------
+// 0: the set nu(l, v), l < p, v < dp does not have the form (or d < 3, where
+// the channels are as cheap); 1: a cubic; 2: with single-variate terms of
+// degree 4 or 5
+template <typename Nu>
+__host__ __device__ constexpr int cubic_kind(const Nu &nu, int p, int dp)
+{
+    if (dp < 4) return 0;
+    int top = 0;
+    for (int l = 0; l < p; ++l) {
+        int deg = 0, parts = 0;
+        for (int v = 0; v < dp; ++v) {
+            deg += nu(l, v);
+            parts += nu(l, v) > 0;
+        }
+        if (deg > 3 && (parts > 1 || deg > 5)) return 0;
+        if (deg > top) top = deg;
+    }
+    // (at degree 2 the Hessian is constant and the channels cost less)
+    return top < 3 ? 0 : top == 3 ? 1 : 2;
+}
+template <int DP, int ETA, int Q>
+constexpr int cubic_kind_of()
+{
+    using BS = Basis<DP, ETA, Q>;
+    return cubic_kind([](int l, int v) { return (int)BS::tab.nu[l][v]; }, BS::P, DP);
+}
+struct CubicLayout {
+    int pairs, rows, ka;       // Hessian pairs, rows at tau, coefficients a row
+    int pairs_t, rows_t, kt;   // the same for u(T, x)
+    int off_t, off_q, total;   // entries before the u(T, x) part and before the
+                               // terms of degree 4 and 5; entries of the table
+    __host__ __device__ constexpr CubicLayout(int d, bool fp32, int kind)
+        : pairs((d + 1) * (d + 2) / 2), rows(pairs + d + 2), ka(d + 2),
+          pairs_t(d * (d + 1) / 2), rows_t(pairs_t + 1), kt(d + 1),
+          off_t(fp32 ? groups(rows) * 4 * ka : rows * ka),
+          off_q(fp32 ? (off_t + groups(rows_t) * 4 * kt + 63) / 64 * 64
+                     : off_t + binom(d + 3, 3)),
+          total(off_q + (kind == 2 ? 2 * (d + 1) : 0))
+    {
+    }
+    // groups of four rows
+    __host__ __device__ static constexpr int groups(int r) { return (r + 3) / 4; }
+};
+
+// ---------------------------------------------------------------------------
 // Per-launch parameters of the path kernel (passed by value).
 // ---------------------------------------------------------------------------
 enum VolKind { kVolConst = 0, kVolBump = 1, kVolDupire = 2 };

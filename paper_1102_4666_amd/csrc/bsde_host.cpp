@@ -313,6 +313,112 @@ void setup_stream_put(hipStream_t s)
 }
 } // namespace
 
+// The rows of a problem's table in the cubic form (bsde_common.h) as
+// combinations of the Chebyshev coefficients, in table order: put(row,
+// factor) takes one entry.
+template <typename Put>
+static void cubic_rows(int d, bool fp32, int kind,
+                       const std::map<std::vector<int8_t>, int> &pos, Put &&put)
+{
+    using Row = std::map<int, double>;
+    const int dp = d + 1;
+    // monomial coefficients of u, those of T_0 .. T_5 being
+    static const double cheb[6][6] = {{1, 0, 0, 0, 0, 0},   {0, 1, 0, 0, 0, 0},
+                                      {-1, 0, 2, 0, 0, 0},  {0, -3, 0, 4, 0, 0},
+                                      {1, 0, -8, 0, 8, 0},  {0, 5, 0, -20, 0, 16}};
+    std::map<std::vector<int8_t>, Row> mono; // at tau
+    for (const auto &f : pos) {
+        std::vector<std::pair<std::vector<int8_t>, double>> terms(
+            1, {std::vector<int8_t>(dp, 0), 1.0});
+        for (int v = 0; v < dp; ++v) {
+            const int a = f.first[v];
+            if (a == 0) continue;
+            std::vector<std::pair<std::vector<int8_t>, double>> next;
+            for (const auto &t : terms)
+                for (int b = a & 1; b <= a; b += 2) {
+                    next.push_back(t);
+                    next.back().first[v] = (int8_t)b;
+                    next.back().second *= cheb[a][b];
+                }
+            terms.swap(next);
+        }
+        for (const auto &t : terms) mono[t.first][f.second] += t.second;
+    }
+    std::map<std::vector<int8_t>, Row> mono_t; // at T: z_0 = 1
+    for (const auto &m : mono) {
+        std::vector<int8_t> mu = m.first;
+        mu[0] = 0;
+        Row &r = mono_t[mu];
+        for (const auto &x : m.second) r[x.first] += x.second;
+    }
+    // the derivative at 0 along the variates of `by`: the monomial's
+    // coefficient times the factorials of its exponents
+    auto at0 = [&](std::map<std::vector<int8_t>, Row> &m, std::initializer_list<int> by,
+                   double f) -> std::pair<const Row *, double> {
+        std::vector<int8_t> mu(dp, 0);
+        for (int v : by) f *= ++mu[v]; // 1, then 2, then 3 of the same variate
+        return {&m[mu], f};
+    };
+    auto put_row = [&](std::pair<const Row *, double> e) {
+        put(std::vector<std::pair<int, double>>(e.first->begin(), e.first->end()), e.second);
+    };
+    const CubicLayout lay(d, fp32, kind);
+    auto row_tau = [&](int r, int k) { // coefficient k (0: constant) of row r
+        if (r < lay.pairs) {
+            const int v = hess_j(dp, r), w = hess_k(dp, r);
+            return k == 0 ? at0(mono, {v, w}, 1.0) : at0(mono, {v, w, k - 1}, 1.0);
+        }
+        if (r < lay.pairs + dp) {
+            const int v = r - lay.pairs;
+            return k == 0 ? at0(mono, {v}, 1.0) : at0(mono, {v, k - 1}, 0.5);
+        }
+        return k == 0 ? at0(mono, {}, 1.0) : at0(mono, {k - 1}, 1.0 / 3.0);
+    };
+    auto row_t = [&](int r, int k) {
+        if (r < lay.pairs_t) {
+            const int v = 1 + hess_j(d, r), w = 1 + hess_k(d, r);
+            const double f = v == w ? 1.0 : 2.0;
+            return k == 0 ? at0(mono_t, {v, w}, f / 2.0) : at0(mono_t, {v, w, k}, f / 6.0);
+        }
+        return k == 0 ? at0(mono_t, {}, 1.0) : at0(mono_t, {k}, 1.0);
+    };
+    static const Row empty;
+    const std::pair<const Row *, double> none{&empty, 0.0};
+    if (fp32) {
+        int e = 0;
+        for (int part = 0; part < 2; ++part) {
+            const int rows = part ? lay.rows_t : lay.rows, nk = part ? lay.kt : lay.ka;
+            for (int g = 0; g < CubicLayout::groups(rows); ++g)
+                for (int k = 0; k < nk; ++k)
+                    for (int r = 4 * g; r < 4 * g + 4; ++r, ++e)
+                        put_row(r >= rows ? none : part ? row_t(r, k) : row_tau(r, k));
+        }
+        for (; e < lay.off_q; ++e) put_row(none);
+    }
+    for (int r = 0; r < lay.rows && !fp32; ++r)
+        for (int k = 0; k < lay.ka; ++k) put_row(row_tau(r, k));
+    // coefficients of the monomials themselves
+    auto coef = [&](std::map<std::vector<int8_t>, Row> &m, std::initializer_list<int> by) {
+        std::vector<int8_t> mu(dp, 0);
+        for (int v : by) ++mu[v];
+        return std::pair<const Row *, double>{&m[mu], 1.0};
+    };
+    if (!fp32) {
+        put_row(coef(mono_t, {}));
+        for (int j = 1; j <= d; ++j) {
+            put_row(coef(mono_t, {j}));
+            for (int k = j; k <= d; ++k) {
+                put_row(coef(mono_t, {j, k}));
+                for (int l = k; l <= d; ++l) put_row(coef(mono_t, {j, k, l}));
+            }
+        }
+    }
+    for (int v = 0; v <= d && kind == 2; ++v) {
+        put_row(coef(mono, {v, v, v, v}));
+        put_row(coef(mono, {v, v, v, v, v}));
+    }
+}
+
 // The points of Picard iteration k.  Uniform kind: n points uniform over
 // [0, T] x D.  Otherwise time-major (point i = a n_spatial + b):
 // time nodes a T / (n_t - 1); tensor grid digits equispaced in [-1, 1]; or
@@ -929,22 +1035,28 @@ bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
             }
             csr_ptr.push_back((int)csr_col.size());
         };
-        for (int l = 0; l < h->p; ++l) put(SRow{{l, 1.0}}, 1.0);
-        for (int c = 2 + d; c < h->C; ++c) {
-            const int j = hess_j(d, c - 2 - d), k = hess_k(d, c - 2 - d);
-            for (int l = 0; l < h->p; ++l) {
-                if (!live(l, c)) continue;
-                // row l of (d/dx_j)(d/dx_k): sum over the middle function mm,
-                // in ascending order
-                std::map<int, double> acc;
-                for (const auto &x1 : h->Dx[j][l])
-                    for (const auto &x2 : h->Dx[k][x1.first]) acc[x2.first] += x1.second * x2.second;
-                put(SRow(acc.begin(), acc.end()), 1.0);
+        const int kind = cubic_kind(
+            [&](int l, int v) { return (int)h->nu[(size_t)l * dp + v]; }, h->p, dp);
+        if (kind > 0) {
+            cubic_rows(d, precision == BSDE_FP32_PATHS, kind, pos, put);
+        } else {
+            for (int l = 0; l < h->p; ++l) put(SRow{{l, 1.0}}, 1.0);
+            for (int c = 2 + d; c < h->C; ++c) {
+                const int j = hess_j(d, c - 2 - d), k = hess_k(d, c - 2 - d);
+                for (int l = 0; l < h->p; ++l) {
+                    if (!live(l, c)) continue;
+                    // row l of (d/dx_j)(d/dx_k): sum over the middle function mm,
+                    // in ascending order
+                    std::map<int, double> acc;
+                    for (const auto &x1 : h->Dx[j][l])
+                        for (const auto &x2 : h->Dx[k][x1.first]) acc[x2.first] += x1.second * x2.second;
+                    put(SRow(acc.begin(), acc.end()), 1.0);
+                }
             }
+            for (int l = 0; l < h->p; ++l)
+                for (int c = 1; c < 2 + d; ++c)
+                    if (live(l, c)) put(Dv[c - 1][l], c == 1 ? tfac : b.scale[c - 2]);
         }
-        for (int l = 0; l < h->p; ++l)
-            for (int c = 1; c < 2 + d; ++c)
-                if (live(l, c)) put(Dv[c - 1][l], c == 1 ? tfac : b.scale[c - 2]);
         h->n_live = (int)csr_ptr.size() - 1;
     }
 

@@ -337,6 +337,245 @@ __device__ __forceinline__ void fill_path_tables()
 }
 
 // ---------------------------------------------------------------------------
+// u, d_t u, grad u and grad^2 u by the cubic form (bsde_common.h) at the
+// mapped coordinates z, folded into u and the frozen generator gen = d_t u +
+// b grad u + tr(a grad^2 u), a_jk = sg_j sg_k C_jk / 2, with bst and sg in
+// units of z, tz = dz_0/dt and rho the correlation; and u(T, x) at the spatial
+// coordinates zT.  table: the problem's table (uniform address).
+//
+// FP32: every row is one row of a 4 x 4 x 1 matrix product of 16 blocks
+// (v_mfma_f32_4x4x1_16b_f32), in which each lane's column is its own path and
+// the four rows of the product land in the lane's own registers.  The rows'
+// coefficients come 64 at a time in one register (one coalesced load), and
+// each product broadcasts one of its 16 groups of four to every block.  A
+// product issues in 4 cycles and does 4 fused multiply-adds a lane on the
+// matrix cores beside the other waves' vector work; with the coefficient as
+// scalar operand each costs the vector unit 4 cycles.  All 64 lanes have to
+// be active (the loads serve the other lanes' products).
+// FP64: rows as fused multiply-adds with scalar operands.
+// ---------------------------------------------------------------------------
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <int D, typename Real>
+struct CubicFold {
+    static constexpr int DP = D + 1;
+    const Real *z, *sg, *bst;
+    const Real tz, rho;
+    Real q[DP], u, gen, off;
+    __device__ __forceinline__ CubicFold(const Real *z_, const Real *sg_, const Real *bst_,
+                                         Real tz_, Real rho_)
+        : z(z_), sg(sg_), bst(bst_), tz(tz_), rho(rho_), u(0), gen(0), off(0)
+    {
+#pragma unroll
+        for (int v = 0; v < DP; ++v) q[v] = Real(0);
+    }
+    // adds d_v u = g to gen and z_v g / f to u
+    template <int V>
+    __device__ __forceinline__ void gradient(Real g, Real f)
+    {
+        u = fma(z[V], f * g, u);
+        gen = fma(V == 0 ? tz : bst[V == 0 ? 0 : V - 1], g, gen);
+    }
+    // row R of the table's rows at tau
+    template <int R>
+    __device__ __forceinline__ void row(Real h)
+    {
+        constexpr int pairs = DP * (DP + 1) / 2;
+        if constexpr (R < pairs) {
+            constexpr int v = hess_j(DP, R), w = hess_k(DP, R);
+            q[v] = fma(h, z[w], q[v]);
+            if constexpr (v != w) q[w] = fma(h, z[v], q[w]);
+            if constexpr (v > 0) {
+                // tr(a H) = sum_j sg_j (sg_j H_jj / 2 + rho sum_{k > j} sg_k H_jk)
+                if constexpr (v == w) {
+                    gen = fma(Real(0.5) * sg[v - 1] * sg[v - 1], h, gen);
+                    off = Real(0);
+                } else {
+                    off = fma(sg[w - 1], h, off);
+                    if constexpr (w == D) gen = fma(rho * sg[v - 1], off, gen);
+                }
+            }
+        } else if constexpr (R < pairs + DP) {
+            gradient<R - pairs>(h, Real(2.0 / 3.0));
+        } else if constexpr (R == pairs + DP) {
+            u += h;
+        }
+    }
+    // the single-variate terms c4 z^4 + c5 z^5 of variate V (w = c4 + c5 z):
+    // their derivatives are z^3 (4 w + c5 z) and 4 z^2 (3 w + 2 c5 z)
+    template <int V>
+    __device__ __forceinline__ void quintic(Real c4, Real c5)
+    {
+        const Real x = z[V], x2 = x * x, t = c5 * x, w = t + c4;
+        u = fma(x2 * x2, w, u);
+        gen = fma(V == 0 ? tz : bst[V == 0 ? 0 : V - 1], x2 * x * fma(Real(4), w, t), gen);
+        if constexpr (V > 0)
+            gen = fma(Real(2) * sg[V - 1] * sg[V - 1], x2 * fma(Real(3), w, t + t), gen);
+    }
+    // the parts of the gradient and of u that come with q
+    __device__ __forceinline__ void finish()
+    {
+        static_for<DP>([&](auto vc) {
+            constexpr int v = decltype(vc)::value;
+            gradient<v>(Real(0.5) * q[v], Real(1.0 / 3.0));
+        });
+    }
+};
+
+// the terms of degree 4 and 5 at T (table: c4, c5 of each variate; z_0 = 1
+// there, in the constant)
+template <int D, typename Table, typename Real>
+__device__ __forceinline__ void quintic_terms_t(Table table, const Real *zT, Real &uT)
+{
+    static_for<D>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        const Real x2 = zT[j] * zT[j];
+        uT = fma(x2 * x2, fma(Real(table[2 * j + 3]), zT[j], Real(table[2 * j + 2])), uT);
+    });
+}
+// and at tau
+template <int D, typename Table, typename Real>
+__device__ __forceinline__ void quintic_terms(Table table, CubicFold<D, Real> &f)
+{
+    static_for<D + 1>([&](auto vc) {
+        constexpr int v = decltype(vc)::value;
+        f.template quintic<v>(table[2 * v], table[2 * v + 1]);
+    });
+}
+
+template <int D, int KIND>
+__device__ __forceinline__ void cubic_eval(uint64_t table, const float *z, const float *zT,
+                                           const float *sg, const float *bst, float rho,
+                                           float tz, float &u, float &gen, float &uT)
+{
+    constexpr CubicLayout lay(D, true, KIND);
+    constexpr int kChunks = lay.off_q / 64;
+    constexpr int GB = 2; // groups of rows at a time
+    const auto tab = (const __attribute__((address_space(1))) float *)table + (threadIdx.x & 63);
+    float ch[kChunks];
+    // a few groups of rows at a time: their products do not wait for each
+    // other.  A batch's chunks are loaded during the batch before it; its
+    // rows are folded before the next batch (pin: the sums pass through an
+    // empty asm statement) and nothing moves across, so that two batches'
+    // chunks and one batch's rows are what is live
+    auto rows = [&](auto off, auto nrows, auto nk, const float *v, auto &&fold, auto &&pin) {
+        constexpr int OFF = decltype(off)::value / 4, NR = decltype(nrows)::value,
+                      NK = decltype(nk)::value, NG = CubicLayout::groups(NR);
+        auto load = [&](auto bc) { // the chunks first needed by batch bc
+            constexpr int b = decltype(bc)::value;
+            constexpr int p0 = OFF + GB * b * NK,
+                          p1 = OFF + (GB * b + GB < NG ? GB * b + GB : NG) * NK;
+            constexpr int c0 = b == 0 ? p0 / 16 : (p0 + 15) / 16, c1 = (p1 + 15) / 16;
+            static_for<c1 - c0>([&](auto cc) {
+                constexpr int c = c0 + decltype(cc)::value;
+                ch[c] = tab[64 * c];
+            });
+        };
+        load(std::integral_constant<int, 0>{});
+        static_for<(NG + GB - 1) / GB>([&](auto bc) {
+            constexpr int g0 = decltype(bc)::value * GB, ng = NG - g0 < GB ? NG - g0 : GB;
+            if constexpr (g0 + GB < NG) load(std::integral_constant<int, g0 / GB + 1>{});
+            f32x4 acc[GB];
+#pragma unroll
+            for (int g = 0; g < GB; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+            static_for<NK>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
+                const float b = k == 0 ? 1.0f : v[k == 0 ? 0 : k - 1];
+                static_for<ng>([&](auto gc) {
+                    constexpr int g = decltype(gc)::value;
+                    constexpr int pos = OFF + (g0 + g) * NK + k;
+                    acc[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(ch[pos / 16], b, acc[g], 4,
+                                                                pos % 16, 0);
+                });
+            });
+            static_for<4 * ng>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                if constexpr (4 * g0 + r < NR)
+                    fold(std::integral_constant<int, 4 * g0 + r>{}, acc[r / 4][r % 4]);
+            });
+            pin();
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    using std::integral_constant;
+    float t = 0.f;
+    uT = 0.f;
+    rows(integral_constant<int, lay.off_t>{}, integral_constant<int, lay.rows_t>{},
+         integral_constant<int, lay.kt>{}, zT, [&](auto rc, float h) {
+             constexpr int r = decltype(rc)::value;
+             if constexpr (r < lay.pairs_t) {
+                 constexpr int j = hess_j(D, r), k = hess_k(D, r);
+                 t = k == j ? h * zT[k] : fmaf(h, zT[k], t);
+                 if constexpr (k == D - 1) uT = fmaf(zT[j], t, uT);
+             } else {
+                 uT += h;
+             }
+         },
+         [&]() { asm volatile("" : "+v"(t), "+v"(uT)); });
+    const auto terms = (const __attribute__((address_space(4))) float *)table + lay.off_q;
+    if constexpr (KIND == 2) {
+        quintic_terms_t<D>(terms, zT, uT);
+        asm volatile("" : "+v"(uT));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    CubicFold<D, float> f(z, sg, bst, tz, rho);
+    rows(integral_constant<int, 0>{}, integral_constant<int, lay.rows>{},
+         integral_constant<int, lay.ka>{}, z, [&](auto rc, float h) {
+             f.template row<decltype(rc)::value>(h);
+         },
+         [&]() {
+             asm volatile("" : "+v"(f.u), "+v"(f.gen), "+v"(f.off));
+#pragma unroll
+             for (int v = 0; v <= D; ++v) asm volatile("" : "+v"(f.q[v]));
+         });
+    if constexpr (KIND == 2) quintic_terms<D>(terms, f);
+    f.finish();
+    u = f.u;
+    gen = f.gen;
+}
+
+template <int D, int KIND>
+__device__ __forceinline__ void cubic_eval(uint64_t table, const double *z, const double *zT,
+                                           const double *sg, const double *bst, double rho,
+                                           double tz, double &u, double &gen, double &uT)
+{
+    constexpr CubicLayout lay(D, false, KIND);
+    const auto tab = (const __attribute__((address_space(4))) double *)table;
+    // u(T, x), nested
+    {
+        int e = lay.off_t;
+        uT = tab[e++];
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            double a = tab[e++];
+#pragma unroll
+            for (int k = j; k < D; ++k) {
+                double b = tab[e++];
+#pragma unroll
+                for (int l = k; l < D; ++l) b = fma(zT[l], tab[e++], b);
+                a = fma(zT[k], b, a);
+            }
+            uT = fma(zT[j], a, uT);
+        }
+    }
+    CubicFold<D, double> f(z, sg, bst, tz, rho);
+    static_for<lay.rows>([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        double h = tab[r * lay.ka];
+#pragma unroll
+        for (int v = 0; v <= D; ++v) h = fma(z[v], tab[r * lay.ka + 1 + v], h);
+        f.template row<r>(h);
+    });
+    if constexpr (KIND == 2) {
+        quintic_terms_t<D>(tab + lay.off_q, zT, uT);
+        quintic_terms<D>(tab + lay.off_q, f);
+    }
+    f.finish();
+    u = f.u;
+    gen = f.gen;
+}
+
+// ---------------------------------------------------------------------------
 // The Monte Carlo path kernel.
 // Grid: n * groups workgroups of kBlock lanes; workgroup (i, g) runs the
 // paths m = (g * ppl + r) * kBlock + lane, r < ppl, m < M, of point i and
@@ -361,22 +600,28 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
     constexpr int SG = (D % 4 == 0) ? 1 : ((D % 2 == 0) ? 2 : 4);
     constexpr int NB = SG * D / 4;
     constexpr int NBB = (D + 3) / 4; // bridge blocks
+    constexpr int kCubicKind = OP == kOpBasis ? cubic_kind_of<DP, ETA, Q>() : 0;
+    constexpr bool kCubic = kCubicKind > 0;
     // Normals of a group of several blocks are made at the first step that
     // needs them: later steps' normals do not wait in registers (the FP64
     // d = 5 kernel keeps its Euler loop free of spills), and a path's last
     // group makes no block beyond its last step.  Not at d = 10, two steps a
-    // group: at the FP64 kernel's two waves per SIMD the blocks made together
+    // group: at the FP64 kernels' two waves per SIMD the blocks made together
     // hide each other's latencies (8192 points, M = 500, N = 50: 4.49 ms
-    // against 4.95), and the FP32 kernel would spill more.
-    constexpr bool kLateNormals = NB > 1 && D < 10;
+    // against 4.95), and the FP32 kernels would spill more; the FP64 ones
+    // outside the cubic form (degree 2) would spill more made together.
+    constexpr bool kLateNormals =
+        NB > 1 && (D < 10 || (sizeof(Real) == 8 && !kCubic));
     constexpr bool kXor3 = sizeof(Real) == 4 || D >= 2; // Philox XOR form
     // FP32 round keys in vector registers (16 of them): at d = 1, and at
     // d = 2 from eta = 5 on, where the kernel's own registers already hold
     // it to four waves per SIMD and the keys still fit (below, they would
     // cost waves).  Not in the kernel operator, whose pair loop, not the
-    // Euler loop, sets the time and which would lose waves.
+    // Euler loop, sets the time and which would lose waves.  At d = 10 in the
+    // cubic form, which leaves the registers for it at three waves (with the
+    // constants of kVecConst: 8192 points, M = 500, N = 50 1.57 -> 1.50 ms).
     constexpr bool kVKeys = sizeof(Real) == 4 && OP == kOpBasis &&
-                            (D == 1 || (D == 2 && ETA >= 5));
+                            (D == 1 || (D == 2 && ETA >= 5) || (D >= 10 && kCubic));
 
     const uint32_t k0 = (uint32_t)prm.seed, k1 = (uint32_t)(prm.seed >> 32);
     PhiloxKeys kv{};
@@ -415,21 +660,24 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
     const Real hk = ES::kappa * h;
     // The volatility levels as vector operands: the volatility's fused
     // multiply-add has another scalar operand (level a) already, and a
-    // second one costs a register move per asset and step.  At d = 10 the
-    // vector registers are the scarcer ones (the moves are cheaper than the
-    // spills that ten more live registers cause).
+    // second one costs a register move per asset and step.  At d = 10
+    // outside the FP32 cubic form the vector registers are the scarcer ones
+    // (the moves are cheaper than the spills that ten more live registers
+    // cause).
+    constexpr bool kVecLevel = D <= 5 || (sizeof(Real) == 4 && kCubic);
     Real lev[D];
 #pragma unroll
     for (int j = 0; j < D; ++j) {
         lev[j] = ac.level[j];
-        if constexpr (D <= 5) asm volatile("" : "+v"(lev[j]));
+        if constexpr (kVecLevel) asm volatile("" : "+v"(lev[j]));
     }
     // gfx950 issues a 32-bit vector instruction whose operands are all
     // vector registers in two cycles, one with a scalar or literal operand
-    // in four.  The FP32 kernels up to d = 5 therefore also hold the other
-    // loop-invariant operands of the Euler step (level a, (r - delta) h
-    // kappa) and the constants of the uniform map in vector registers.
-    constexpr bool kVecConst = sizeof(Real) == 4 && D <= 5;
+    // in four.  The FP32 kernels up to d = 5 and in the cubic form therefore
+    // also hold the other loop-invariant operands of the Euler step (level a,
+    // (r - delta) h kappa) and the constants of the uniform map in vector
+    // registers.
+    constexpr bool kVecConst = sizeof(Real) == 4 && kVecLevel;
     Real lva[D], dhk[D];
 #pragma unroll
     for (int j = 0; j < D; ++j) {
@@ -451,10 +699,16 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
     // path by path (Welford), so the sum of squares never dwarfs the spread
     int cnt = 0;
     double mean = 0.0, m2 = 0.0;
+    // FP32 paths on the cubic form use the matrix cores, whose products need
+    // every lane of the wave: its lanes beyond M run a path that is not counted
+    constexpr bool kWholeWave = kCubic && sizeof(Real) == 4;
     for (int rr = 0; rr < prm.paths_per_lane; ++rr) {
         int m = (g * prm.paths_per_lane + rr) * kBlock + (int)threadIdx.x;
-        const bool valid = m < prm.M;
-        if (!valid) break;
+        if constexpr (kWholeWave) {
+            if (__builtin_amdgcn_readfirstlane(m & ~63) >= prm.M) break;
+        } else {
+            if (m >= prm.M) break;
+        }
 
         // U, j* = floor(U N) and theta = U N - j* in integer arithmetic
         const u32x4 wu = block((uint32_t)m, 1u << 24);
@@ -573,17 +827,6 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
                     sgs[j] * fma(theta, LGs[j], lgb);
         }
 
-        // basis row at (tau, X_tau) contracted with the channel table, and
-        // the value u^k(T, X_T) (z_0 = 1 there, so every T_a(z_0) = 1)
-        Real Tz[DP][ETA + 1], TzT[DP][ETA + 1];
-        cheb<ETA>(tau * tscale - Real(1), Tz[0]);
-#pragma unroll
-        for (int a = 0; a <= ETA; ++a) TzT[0][a] = Real(1);
-#pragma unroll
-        for (int j = 0; j < D; ++j) {
-            cheb<ETA>((Xt[j] - ac.mid[j]) * ac.scale[j], Tz[1 + j]);
-            cheb<ETA>((X[j] - ac.mid[j]) * ac.scale[j], TzT[1 + j]);
-        }
         // payoff at tau (for the penalty) and the terminal term
         // Phi(X_T) - u^k(T, X_T)
         Real phi_tau = payoff<D>(prm.payoff, K, Xt);
@@ -688,8 +931,38 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
             gen = acc / S0;
             uT = S1T / S0T;
             terminal = payoff<D>(prm.payoff, K, X) - uT;
+        } else if constexpr (kCubic) {
+            if constexpr (D >= 5) asm volatile("" : "+v"(phi_tau));
+            terminal = payoff<D>(prm.payoff, K, X);
+            Real z[DP], zT[D], sz[D], bz[D];
+            z[0] = fma(tau, tscale, Real(-1));
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                z[1 + j] = (Xt[j] - ac.mid[j]) * ac.scale[j];
+                zT[j] = (X[j] - ac.mid[j]) * ac.scale[j];
+                sz[j] = sgs[j] * ac.scale[j];
+                bz[j] = bst[j] * ac.scale[j];
+            }
+            // (the table's address is made opaque once per path, so that its
+            // loads stay in the path's iteration instead of being hoisted out
+            // of the path loop into registers)
+            uint64_t pa = (uint64_t)(uintptr_t)&gamma[0];
+            asm volatile("" : "+s"(pa));
+            cubic_eval<D, kCubicKind>(pa, z, zT, sz, bz, rho, tscale, u, gen, uT);
+            terminal -= uT;
         } else {
             if constexpr (D >= 5) asm volatile("" : "+v"(phi_tau));
+            // basis row at (tau, X_tau) contracted with the channel table,
+            // and the value u^k(T, X_T) (z_0 = 1 there, so every T_a(z_0) = 1)
+            Real Tz[DP][ETA + 1], TzT[DP][ETA + 1];
+            cheb<ETA>(tau * tscale - Real(1), Tz[0]);
+#pragma unroll
+            for (int a = 0; a <= ETA; ++a) TzT[0][a] = Real(1);
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                cheb<ETA>((Xt[j] - ac.mid[j]) * ac.scale[j], Tz[1 + j]);
+                cheb<ETA>((X[j] - ac.mid[j]) * ac.scale[j], TzT[1 + j]);
+            }
             // basis function l as the product of its non-zero Chebyshev
             // factors (at most eta of them), so that no earlier basis value
             // has to stay live in registers
@@ -781,6 +1054,8 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
         const Real f = -r * u + omega * fmax(phi_tau - u, Real(0));
         const Real a = (T - t0) * (f + gen) + terminal;
         const double ad = (double)a;
+        if constexpr (kWholeWave)
+            if (m >= prm.M) continue;
         cnt += 1;
         const double dev = ad - mean;
         mean += dev / (double)cnt;
