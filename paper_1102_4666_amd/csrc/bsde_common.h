@@ -227,11 +227,13 @@ __host__ __device__ constexpr int num_channels(int d)
 __host__ __device__ constexpr int pad16(int x) { return (x + 15) & ~15; }
 
 // The channel table the path kernels read (FP64 and FP32 alike) holds the
-// live rows of the p x C table packed (see channel_row_live) in three
+// live rows of the p x C table packed (see channel_row_live) in four
 // blocks: channel 0 over every row (p entries); each second-derivative
 // channel over its live rows, channel after channel; then row after row the
 // live entries of channels 1 .. 1 + d (the time derivative and the
-// gradient), in channel order -- at most p C entries in all.
+// gradient), in channel order; then the coefficients of u(T, x) over the
+// spatial functions (z_0 = 1 there: the sums over the time degrees), in the
+// order of the rows with time degree zero -- at most p C entries in all.
 __host__ __device__ constexpr size_t table_entries(int p, int C)
 {
     return (size_t)p * C;

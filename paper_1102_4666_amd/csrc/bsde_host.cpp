@@ -1015,8 +1015,8 @@ bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
     // the packed channel table (bsde_common.h) as a sparse matrix over the
     // coefficients, in the order the path kernels read it: channel 0; each
     // second derivative over its live rows; then row by row the time
-    // derivative and the gradient.  The kernel's index set is the set of
-    // rows here.
+    // derivative and the gradient; then u(T, x).  The kernel's index set is
+    // the set of rows here.
     std::vector<int> csr_ptr(1, 0), csr_col;
     std::vector<double> csr_val;
     if (!kop) {
@@ -1056,6 +1056,17 @@ bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
             for (int l = 0; l < h->p; ++l)
                 for (int c = 1; c < 2 + d; ++c)
                     if (live(l, c)) put(Dv[c - 1][l], c == 1 ? tfac : b.scale[c - 2]);
+            // u(T, x): the functions of every time degree over each spatial one
+            for (int l = 0; l < h->p; ++l) {
+                if (h->nu[(size_t)l * dp] != 0) continue;
+                std::vector<int8_t> mu(&h->nu[(size_t)l * dp], &h->nu[(size_t)l * dp] + dp);
+                SRow r;
+                for (; mu[0] <= grid->eta; ++mu[0]) {
+                    const auto it = pos.find(mu);
+                    if (it != pos.end()) r.push_back({it->second, 1.0});
+                }
+                put(r, 1.0);
+            }
         }
         h->n_live = (int)csr_ptr.size() - 1;
     }

@@ -221,6 +221,15 @@ __device__ __forceinline__ void cheb(Real z, Real *Tz)
     for (int a = 1; a < ETA; ++a) Tz[a + 1] = Real(2) * z * Tz[a] - Tz[a - 1];
 }
 
+// Position of row l (time degree zero) among the rows with time degree zero
+template <typename BS>
+constexpr int terminal_index(int l)
+{
+    int n = 0;
+    for (int q = 0; q < l; ++q) n += BS::tab.nu[q][0] == 0;
+    return n;
+}
+
 // One Philox4x32-10 round in the path kernel (the function of philox_round).
 // Bit 0 / bit 1 of X3 select, for the new word 0 / word 2, the three-way
 // XOR (high half ^ counter word ^ key) as one v_bitop3_b32 with truth table
@@ -1010,10 +1019,14 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
                 uint64_t pa = (uint64_t)(uintptr_t)&gamma[0];
                 asm volatile("" : "+s"(pa));
                 const auto pk = (const __attribute__((address_space(4))) Real *)pa;
-                // u^k(T, X_T): channel 0
+                // u^k(T, X_T): z_0 = 1, so the functions of each spatial
+                // multi-index share one coefficient, their sum (after the
+                // channels in the table, in the order of the rows with time
+                // degree zero)
                 static_for<NP>([&](auto lc) {
                     constexpr int l = decltype(lc)::value;
-                    uT = fma(basis(lc, TzT), pk[l], uT);
+                    if constexpr (BS::tab.nu[l][0] == 0)
+                        uT = fma(basis(lc, TzT), pk[CR::tab.goff[NP] + terminal_index<BS>(l)], uT);
                 });
                 terminal = payoff<D>(prm.payoff, K, X) - uT;
                 // second derivatives first, one channel at a time, each
