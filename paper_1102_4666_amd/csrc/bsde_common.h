@@ -482,6 +482,7 @@ struct PathParams {
     AssetConsts<float> cf;     // the per-asset constants in FP32
     AssetConsts<double> cd;    // and in FP64
     double kbw;                // kernel operator: bandwidth in z (0: least squares)
+    int kop_nt;                // its time nodes in a product table (0: plain rows)
 };
 
 // Extrapolating operators: least squares on the polynomial basis, or the
@@ -491,6 +492,24 @@ enum { kOpBasis = 0, kOpKernel = 1 };
 constexpr int kKernelRow = 4;
 // weights beyond this exponent are constant (the clamp of the kernel)
 constexpr double kKernelClamp = 60.0;
+// Points that are every spatial point at every one of nt <= kKopTimes time
+// nodes (the tensor and random kinds) have a product table instead: z_0 of
+// the node and its weight factor at z_0 = 1 for each time node (2 kKopTimes
+// entries), then for each of the ns spatial points a row {z_1 .. z_d, y at
+// time node 0, 1, ..}.
+constexpr int kKopTimes = 16;
+__host__ __device__ constexpr int kop_row(int d, int nt) { return (d + nt + 3) / 4 * 4; }
+// entries of a kernel operator's table of n points (nt as in kop_nt)
+__host__ __device__ constexpr size_t kop_entries(int d, int n, int nt)
+{
+    return nt ? 2 * kKopTimes + (size_t)(n / nt) * kop_row(d, nt) : (size_t)n * kKernelRow;
+}
+// entry of the table that holds y of point i
+__host__ __device__ constexpr size_t kop_value(int d, int n, int nt, int i)
+{
+    return nt ? 2 * kKopTimes + (size_t)(i % (n / nt)) * kop_row(d, nt) + d + i / (n / nt)
+              : (size_t)i * kKernelRow + 1 + d;
+}
 
 template <typename Real>
 __host__ __device__ __forceinline__ const AssetConsts<Real> &asset_consts(const PathParams &p);

@@ -969,6 +969,7 @@ bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
     h->n_t = n_t;
     h->n_x = grid->n_x;
     h->redraw = grid->redraw;
+    b.kop_nt = kop && grid->kind != BSDE_GRID_UNIFORM && n_t <= kKopTimes ? n_t : 0;
     h->pts_k = 0;
     make_points(h, 0, h->pts);
 
@@ -1093,7 +1094,7 @@ bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
                  b_g32 = sizeof(float) * table_floats(h),
                  b_ptr = kop ? 0 : sizeof(int) * csr_ptr.size(),
                  b_col = sizeof(int) * csr_col.size(),
-                 b_ktab = kop ? real_size * kKernelRow * (size_t)h->n : 0;
+                 b_ktab = kop ? real_size * kop_entries(d, h->n, b.kop_nt) : 0;
     const size_t o_val = al256(b_pts), o_alpha = o_val + al256(b_val),
                  o_g64 = o_alpha + al256(b_alpha), o_g32 = o_g64 + al256(b_g64),
                  o_ptr = o_g32 + al256(b_g32), o_col = o_ptr + al256(b_ptr),
@@ -1121,22 +1122,30 @@ bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
         h->d_cols = b_ptr ? (int *)(b + o_col) : nullptr;
         h->d_ktab = kop ? (void *)(b + o_ktab) : nullptr;
     }
-    // the kernel operator's table: rows {z_0, .., z_d, y = 0} in the path
-    // precision, z the mapped coordinates of the points
+    // the kernel operator's table in the path precision (bsde_common.h), y = 0
     std::vector<unsigned char> ktab(b_ktab, 0);
+    auto set_ktab = [&](size_t e, double v) {
+        const float f = (float)v;
+        if (real_size == sizeof(float)) std::memcpy(&ktab[e * sizeof(f)], &f, sizeof(f));
+        else std::memcpy(&ktab[e * sizeof(v)], &v, sizeof(v));
+    };
     for (int i = 0; kop && i < h->n; ++i) {
-        double z[kKernelRow] = {0, 0, 0, 0};
+        double z[kMaxD + 1];
         z[0] = 2.0 * h->pts[(size_t)i * dp] / payoff->T - 1.0;
         for (int j = 0; j < d; ++j)
             z[1 + j] = (h->pts[(size_t)i * dp + 1 + j] - b.mid[j]) * b.scale[j];
-        for (int v = 0; v < kKernelRow; ++v) {
-            if (real_size == sizeof(float)) {
-                const float f = (float)z[v];
-                std::memcpy(&ktab[((size_t)i * kKernelRow + v) * real_size], &f, sizeof(f));
-            } else {
-                std::memcpy(&ktab[((size_t)i * kKernelRow + v) * real_size], &z[v], sizeof(double));
-            }
+        if (b.kop_nt == 0) {
+            for (int v = 0; v <= d; ++v) set_ktab((size_t)i * kKernelRow + v, z[v]);
+            continue;
         }
+        if (i % h->n_spatial == 0) {
+            const int a = i / h->n_spatial;
+            set_ktab(2 * a, z[0]);
+            set_ktab(2 * a + 1, std::exp(-(1.0 - z[0]) * (1.0 - z[0]) * 0.5 / (b.kbw * b.kbw)));
+        }
+        if (i < h->n_spatial)
+            for (int j = 0; j < d; ++j)
+                set_ktab(kop_value(d, h->n, b.kop_nt, i) - d + j, z[1 + j]);
     }
     // uploads and the set-up kernels go to a set-up stream of the library
     // (non-blocking: a problem created while another one solves does not

@@ -136,15 +136,16 @@ __global__ __launch_bounds__(256) void batch_channel_kernel(
 // y^k_i = u^k(t_i, x_i) + c^k_i with u^k = h[y^{k-1}] = sum_j y_j w_j /
 // sum_j w_j (FP64), w_j = exp(-min(|z_i - z_j|^2 / (2 b^2), clamp)) in the
 // mapped coordinates; yprev null for u^k = 0.  Writes y^k (FP64) and the y
-// column of the path kernel's table (FP32 or FP64).  One lane per point;
-// the loop over the points j is uniform (scalar loads of their rows).
+// entries of the path kernel's table (FP32 or FP64).  A wave per point, the
+// points j over its lanes (n = 512: 8 us; one lane per point left two
+// workgroups with 512 dependent terms each, 128 us).
 __global__ __launch_bounds__(256) void kernel_update_kernel(
     const PathParams prm, int d, const double *__restrict__ pts,
     const double *__restrict__ yprev, const double *__restrict__ c,
     double *__restrict__ ynew, void *__restrict__ table, int fp32)
 {
     const int n = prm.n;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * 4 + ((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (i >= n) return;
     const int dp = d + 1;
     const double inv2b2 = 0.5 / (prm.kbw * prm.kbw);
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(256) void kernel_update_kernel(
     double u = 0.0;
     if (yprev) {
         double S0 = 0.0, S1 = 0.0;
-        for (int q = 0; q < n; ++q) {
+        for (int q = lane; q < n; q += 64) {
             const double *row = pts + (size_t)q * dp;
             double dz = zi[0] - (2.0 * row[0] / prm.T - 1.0);
             double qq = dz * dz;
@@ -167,21 +168,28 @@ __global__ __launch_bounds__(256) void kernel_update_kernel(
             S0 += w;
             S1 += yprev[q] * w;
         }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            S0 += __shfl_xor(S0, off);
+            S1 += __shfl_xor(S1, off);
+        }
         u = S1 / S0;
     }
+    if (lane != 0) return;
     const double y = u + c[i];
     ynew[i] = y;
+    const size_t e = kop_value(d, n, prm.kop_nt, i);
     if (fp32)
-        ((float *)table)[(size_t)i * kKernelRow + 1 + d] = (float)y;
+        ((float *)table)[e] = (float)y;
     else
-        ((double *)table)[(size_t)i * kKernelRow + 1 + d] = y;
+        ((double *)table)[e] = y;
 }
 
 hipError_t launch_kernel_update(const PathParams &prm, int d, const double *pts,
                                 const double *yprev, const double *c, double *ynew,
                                 void *table, int fp32, hipStream_t s)
 {
-    hipLaunchKernelGGL(kernel_update_kernel, dim3((prm.n + 255) / 256), dim3(256), 0, s,
+    hipLaunchKernelGGL(kernel_update_kernel, dim3((prm.n + 3) / 4), dim3(256), 0, s,
                        prm, d, pts, yprev, c, ynew, table, fp32);
     return hipGetLastError();
 }

@@ -892,6 +892,70 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
             Real G0[D], G1[D]; // sum w dz_j and sum y w dz_j (unclamped weights)
 #pragma unroll
             for (int j = 0; j < D; ++j) G0[j] = G1[j] = Real(0);
+            if (prm.kop_nt > 0) {
+                // Product points: e^{-e} of a pair is the product of its
+                // time node's and its spatial point's factors, so a pair
+                // costs a product, a maximum (the clamp: max(e^{-e}, e^{-clamp})
+                // = e^{-min(e, clamp)}) and its share of the sums instead of
+                // two exponentials and the squared distances (FP32, d = 1:
+                // 512 points, M = 1000: 189 -> 109 us).  The path's time
+                // factors wait in LDS; the sums over a spatial point's times
+                // of the unclamped weights and their first moments in dz_0
+                // give the moments in dz_j.
+                __shared__ Real kop_w[OP == kOpKernel ? kKopTimes : 1][kBlock];
+                const int nt = prm.kop_nt, ns = prm.n / nt, stride = kop_row(D, nt);
+                auto factor = [&](Real e) {
+                    if constexpr (kF32) return __builtin_amdgcn_exp2f(-e);
+                    else return ::exp(-e);
+                };
+                const Real wc = factor(clamp);
+                for (int a = 0; a < nt; ++a) {
+                    const Real d0 = zt[0] - gamma[2 * a];
+                    kop_w[a][threadIdx.x] = factor(d0 * d0 * kq);
+                }
+                for (int sp = 0; sp < ns; ++sp) {
+                    const auto row = gamma + (2 * kKopTimes + (size_t)sp * stride);
+                    Real dz[D], e = Real(0), eT = Real(0);
+#pragma unroll
+                    for (int j = 0; j < D; ++j) {
+                        dz[j] = zt[1 + j] - row[j];
+                        e = fma(dz[j], dz[j], e);
+                        const Real dT = zT[1 + j] - row[j];
+                        eT = fma(dT, dT, eT);
+                    }
+                    const Real wx = factor(e * kq), wxT = factor(eT * kq);
+                    // sums over the times: unclamped weights, with y, and both
+                    // with dz_0
+                    Real A0 = 0, B0 = 0, A1 = 0, B1 = 0;
+#pragma unroll 4
+                    for (int a = 0; a < nt; ++a) {
+                        const Real y = row[D + a], d0 = zt[0] - gamma[2 * a];
+                        const Real w = kop_w[a][threadIdx.x] * wx;
+                        const Real wm = fmax(w, wc);
+                        S0 += wm;
+                        S1 = fma(wm, y, S1);
+                        const Real wd = w >= wc ? w : Real(0), wyd = wd * y;
+                        A0 += wd;
+                        B0 += wyd;
+                        A1 = fma(wd, d0, A1);
+                        B1 = fma(wyd, d0, B1);
+                        const Real wT = fmax(gamma[2 * a + 1] * wxT, wc);
+                        S0T += wT;
+                        S1T = fma(wT, y, S1T);
+                    }
+                    Real l = c0;
+#pragma unroll
+                    for (int j = 0; j < D; ++j) {
+                        l = fma(cj[j], dz[j], l);
+#pragma unroll
+                        for (int k = j; k < D; ++k) l = fma(cjk[j][k], dz[j] * dz[k], l);
+                        G0[j] = fma(A0, dz[j], G0[j]);
+                        G1[j] = fma(B0, dz[j], G1[j]);
+                    }
+                    L0 = fma(l, A0, fma(ct, A1, L0));
+                    L1 = fma(l, B0, fma(ct, B1, L1));
+                }
+            } else {
 #pragma unroll 4
             for (int q = 0; q < prm.n; ++q) {
                 const auto row = gamma + (size_t)q * kKernelRow;
@@ -925,6 +989,7 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
                 const Real wT = weight(qT * kq);
                 S0T += wT;
                 S1T = fma(wT, y, S1T);
+            }
             }
             u = S1 / S0;
             // d_j S = -G_j / b^2 (z units), d_j h = (d_j S1 - h d_j S0) / S0
