@@ -370,6 +370,13 @@ hipError_t launch_update(int n, int groups, int M, int ppg, int p, int nnz,
     return hipGetLastError();
 }
 
+hipError_t launch_project(const double *W, const double *c, int n, int p, double *beta,
+                          hipStream_t s)
+{
+    hipLaunchKernelGGL(project_kernel, dim3(p), dim3(256), 0, s, W, c, n, beta);
+    return hipGetLastError();
+}
+
 hipError_t launch_channels(int p, int nnz, hipStream_t s, const double *alpha,
                            const int *rowptr, const int *cols, const double *vals,
                            double *g64, float *g32)
