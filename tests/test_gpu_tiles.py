@@ -1,0 +1,76 @@
+"""How a point's paths are cut into tiles: points at T, whose paths do not
+move, and numbers of paths around a wavefront and a workgroup in one and
+several groups."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1102_4666_amd as bsde
+from workloads import problem
+
+pytestmark = pytest.mark.gpu
+
+# per-point corrections relative to 1 + |c| + standard deviation + |u|
+TOL = {"fp64": 1e-8, "fp32": 2e-3}
+
+
+def _config(d, M, N, prec, **kw):
+    shape = {1: dict(grid="tensor", n_t=6, n_x=9, eta=3), 2: dict(grid="tensor", n_t=7, n_x=8, eta=4),
+             3: dict(grid="random", n_t=5, n_x=30, eta=2), 5: dict(grid="random", n_t=5, n_x=80, eta=3),
+             10: dict(grid="random", n_t=5, n_x=120, eta=2)}[d]
+    return problem(d=d, vol_kind="bump", vol_level=[0.15 + 0.02 * j for j in range(d)], bump_a=0.25,
+                   rho=0.2 if d > 1 else 0.0, payoff="put", S0=100.0, M=M, N=N, K_it=2, omega=1.0,
+                   precision=prec, seed=21, **dict(shape, **kw))
+
+
+def _iterate(cfg):
+    nu = oracle.index_set(cfg["d"] + 1, cfg["eta"])
+    alpha = np.random.default_rng(9).normal(size=len(nu)) * 3.0 * 0.4 ** nu.sum(axis=1)
+    return alpha, oracle.basis_matrix(cfg) @ alpha
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("d", [1, 2, 3, 5, 10])
+def test_points_at_the_end_have_no_spread(d, prec):
+    cfg = _config(d, 700, 7, prec)
+    alpha, y = _iterate(cfg)
+    print("points at T d=%d %s" % (d, prec), flush=True)
+    with bsde.Problem(cfg) as P:
+        P.fit_values(y, 1)
+        P.solve()
+        c, var = P.corrections(1)
+        last = np.flatnonzero(P.points()[:, 0] == cfg["T"])
+    assert len(last) == len(c) // cfg["n_t"]
+    assert np.all(var[last] == 0.0)
+    for i in last[[0, len(last) // 2, -1]]:
+        rc, rv = (float(v[0]) for v in oracle.corrections(cfg, alpha, 1, i, i + 1))
+        assert rv <= 1e-20
+        assert abs(c[i] - rc) <= TOL[prec] * (1.0 + abs(rc) + abs(y[i])), (i, c[i], rc)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("M,tilings", [(1, [(1, 1), (3, 1)]), (64, [(1, 1)]), (65, [(1, 1), (2, 1)]),
+                                       (256, [(1, 1), (8, 1)]), (777, [(1, 4), (2, 2), (4, 1), (8, 2)]),
+                                       (1300, [(1, 6), (3, 2), (5, 2)])])
+def test_moments_do_not_depend_on_the_tiling(M, tilings, prec):
+    cfg = _config(2, M, 5, prec)
+    alpha, y = _iterate(cfg)
+    print("tilings of M=%d %s" % (M, prec), flush=True)
+    with bsde.Problem(cfg) as P:
+        got = []
+        for t in [None] + tilings:
+            P.set_tiling(*(t or (0, 0)))
+            P.fit_values(y, 1)
+            P.solve()
+            got.append(P.corrections(1))
+    # the paths' terms are the same numbers in every tiling; their moments
+    # differ by the rounding of FP64 sums of at most 1300 terms
+    c0, v0 = got[0]
+    for c, v in got[1:]:
+        assert np.all(np.abs(c - c0) <= 1e-12 * (1.0 + np.abs(c0) + np.sqrt(v0)))
+        assert np.all(np.abs(v - v0) <= 1e-11 * (v0 + 1e-12 * (1.0 + c0 ** 2)))
+    for i in (3, len(y) // 2 + 1):
+        rc, rv = (float(v[0]) for v in oracle.corrections(cfg, alpha, 1, i, i + 1))
+        scale = 1.0 + abs(rc) + np.sqrt(rv) + abs(y[i])
+        assert abs(c0[i] - rc) <= TOL[prec] * scale
+        assert abs(v0[i] - rv) <= 4 * TOL[prec] * scale ** 2
