@@ -1148,18 +1148,30 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
             if (m >= prm.M) continue;
         cnt += 1;
         const double dev = ad - mean;
-        mean += dev / (double)cnt;
+        mean = rr == 0 ? ad : mean + dev / (double)cnt;
         m2 = fma(dev, ad - mean, m2);
     }
 
     // fixed-order reduction of the lanes' moments (combine_moments):
     // butterfly within the wavefront, then waves in order through LDS
     double n = (double)cnt;
+    if (__all(cnt == __builtin_amdgcn_readfirstlane(cnt))) {
+        // lanes with as many paths each (every wave but the one that M ends
+        // in): the same combination with its quotients n_b / n = 1/2
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double nb = __shfl_xor(n, off), mb = __shfl_xor(mean, off),
-                     m2b = __shfl_xor(m2, off);
-        combine_moments(n, mean, m2, nb, mb, m2b);
+        for (int off = 32; off > 0; off >>= 1) {
+            const double d = __shfl_xor(mean, off) - mean, m2b = __shfl_xor(m2, off);
+            mean = fma(d, 0.5, mean);
+            m2 = fma(d * d, 0.5 * n, m2 + m2b);
+            n += n;
+        }
+    } else {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const double nb = __shfl_xor(n, off), mb = __shfl_xor(mean, off),
+                         m2b = __shfl_xor(m2, off);
+            combine_moments(n, mean, m2, nb, mb, m2b);
+        }
     }
     __shared__ double red[3][kBlock / 64];
     const int wave = threadIdx.x >> 6;
@@ -1207,13 +1219,19 @@ __global__ __launch_bounds__(kBlock, (min_waves<D, Real>())) void path_kernel(
     const Real *__restrict__ gamma, double *__restrict__ partial)
 {
     const int i = blockIdx.x / prm.groups;
-    const int g = blockIdx.x - i * prm.groups;
+    // Consecutive workgroups go to the 8 XCDs in turn and, within one, to its
+    // 4 shader engines: 32 of them, so that 16 points of two groups or more
+    // meet every engine.  The groups move on by one every 16 points; else the
+    // last group, whose paths end at M, would fall to the same engines at
+    // every point (n = 3000, M = 3000, eight groups of two blocks: 4.2 ms,
+    // 3.2 with the turn).
+    const int g = (blockIdx.x - i * prm.groups + (i >> 4)) % prm.groups;
     fill_path_tables<Real>();
     // prm is the first kernel argument: its copy at the start of the
     // kernel-argument segment is the one the scalar loads read
     run_tile<D, ETA, Real, VOL, Q, const Real *__restrict__, OP, true>(
         prm, (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr(), pts,
-        gamma, i, g, partial + 2 * (size_t)blockIdx.x);
+        gamma, i, g, partial + 2 * ((size_t)i * prm.groups + g));
 }
 
 // Many problems of one kernel signature in one persistent launch.  Tiles
