@@ -85,71 +85,74 @@ __global__ __launch_bounds__(256) void basis_matrix_kernel(
     }
 }
 
-// Partial Gram matrices: workgroup (pair, chunk) -- one wave -- forms the
-// 64 x 64 block (bi, bj), bi <= bj, of A'A over the rows of its chunk.
+// Partial Gram matrices: workgroup (pair, chunk) forms the 64 x 64 block
+// (bi, bj), bi <= bj, of A'A over the rows of its chunk, a wave Q x Q tiles of
+// 16 x 16 of it.  A chunk of 64 rows is one batch of loads, so that its time
+// is their latency once and not four times (n = 1000, p = 221: 23 -> 9 us;
+// n = 81,920, p = 364: 365 -> 266 us).
 // The rows assigned to the four k-slots of an MFMA are permuted so that
 // each lane reads 4 consecutive rows of one column (32 contiguous bytes,
 // a whole 128-byte line per 4 lanes): in step t of a 16-row group at s,
 // k-slot kk takes row s + 4 kk + t, the same for both operands.
 // partial[chunk][r][c] holds the block's entries (r in bi's rows).
-__global__ __launch_bounds__(64) void gram_partial_kernel(
+template <int Q>
+__global__ __launch_bounds__(64 * (4 / Q) * (4 / Q)) void gram_partial_kernel(
     const double *__restrict__ A, int ld, int pap, int rows_per_chunk,
     const int2 *__restrict__ pairs, double *__restrict__ partial)
 {
     const int2 pr = pairs[blockIdx.x];
     const int chunk = blockIdx.y;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // the wave's tiles of the block: Q x Q from (qa, qb)
+    const int qa = 4 * pr.x + Q * (wave / (4 / Q)), qb = 4 * pr.y + Q * (wave % (4 / Q));
     const int r0 = chunk * rows_per_chunk;
     const int r1 = min(ld, r0 + rows_per_chunk);
     const int tiles = pap >> 4;
     int nti = 0, ntj = 0;
-    const double *pa[4], *pb[4];
+    const double *pa[Q], *pb[Q];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int ti = pr.x * 4 + t, tj = pr.y * 4 + t;
+    for (int t = 0; t < Q; ++t) {
+        const int ti = qa + t, tj = qb + t;
         nti += ti < tiles;
         ntj += tj < tiles;
         pa[t] = A + (size_t)(min(ti, tiles - 1) * 16 + (lane & 15)) * ld + 4 * (lane >> 4);
         pb[t] = A + (size_t)(min(tj, tiles - 1) * 16 + (lane & 15)) * ld + 4 * (lane >> 4);
     }
-    f64x4 acc[4][4];
+    f64x4 acc[Q][Q];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < Q; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int b = 0; b < Q; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+    auto load = [&](const double *p, double *v) {
+        const double2 x = *(const double2 *)p, y = *(const double2 *)(p + 2);
+        v[0] = x.x; v[1] = x.y; v[2] = y.x; v[3] = y.y;
+    };
+    // (tiles beyond the last repeat it, and are not stored)
+#pragma unroll 4
     for (int s = r0; s < r1; s += 16) {
-        double va[4][4], vb[4][4];
+        double va[Q][4], vb[Q][4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            if (t < nti) {
-                const double2 x = *(const double2 *)(pa[t] + s);
-                const double2 y = *(const double2 *)(pa[t] + s + 2);
-                va[t][0] = x.x; va[t][1] = x.y; va[t][2] = y.x; va[t][3] = y.y;
-            }
-            if (t < ntj) {
-                const double2 x = *(const double2 *)(pb[t] + s);
-                const double2 y = *(const double2 *)(pb[t] + s + 2);
-                vb[t][0] = x.x; vb[t][1] = x.y; vb[t][2] = y.x; vb[t][3] = y.y;
-            }
+        for (int t = 0; t < Q; ++t) {
+            load(pa[t] + s, va[t]);
+            load(pb[t] + s, vb[t]);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+            for (int a = 0; a < Q; ++a)
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    if (a < nti && b < ntj) acc[a][b] = mma64(va[a][k], vb[b][k], acc[a][b]);
+                for (int b = 0; b < Q; ++b) acc[a][b] = mma64(va[a][k], vb[b][k], acc[a][b]);
     }
     double *out = partial + (size_t)chunk * pap * pap;
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < Q; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < Q; ++b)
             if (a < nti && b < ntj) {
-                const int col = (pr.y * 4 + b) * 16 + (lane & 15);
+                const int col = (qb + b) * 16 + (lane & 15);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int row = (pr.x * 4 + a) * 16 + (lane >> 4) + 4 * v;
+                    const int row = (qa + a) * 16 + (lane >> 4) + 4 * v;
                     out[(size_t)row * pap + col] = acc[a][b][v];
                 }
             }
@@ -309,43 +312,47 @@ __device__ __forceinline__ f64x4 tile_load(const double *m, int ld)
     return t;
 }
 
-// Upper Cholesky factor of a 16 x 16 diagonal tile and the factor's inverse,
-// by one wave (lane c & 15 holds column c; the other lanes repeat it).  d:
-// the tile (row stride 17), replaced by the factor; di: its inverse.  live:
-// rows before the padding.  False when a live pivot is not positive or its
-// square root not above floor.
+// 1 / sqrt(x), x > 0: the hardware estimate y (relative error 2^-24) and the
+// series of (1 - e)^{-1/2}, e = 1 - x y^2, to second order
+__device__ __forceinline__ double rsqrt_pos(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// Upper Cholesky factor R of a 16 x 16 diagonal tile and R^{-1}, by one wave.
+// d: the tile (row stride 17), replaced by R; di: the inverse.  Lane c < 16
+// holds column c of the tile, lane 16 + c column c of the identity (the upper
+// half of the wave repeats them): the row operations that turn the tile into
+// R turn the identity into R^{-T}.  live: rows before the padding.  False
+// when a live pivot is not positive or its square root not above floor.
 __device__ __forceinline__ bool chol_tile(double (*d)[17], double (*di)[17], int live,
                                           double floor)
 {
     const int c = threadIdx.x & 15;
-    double a[16], x[16];
+    const bool unit = threadIdx.x & 16;
+    double a[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) a[r] = d[r][c];
+    for (int r = 0; r < 16; ++r) {
+        const double v = d[r][c];
+        a[r] = unit ? (r == c ? 1.0 : 0.0) : v;
+    }
     bool ok = true;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-        const double piv = lane_value(a[j], j), root = sqrt(piv);
-        if (j < live && (!(piv > 0.0) || !(root > floor))) ok = false;
-        a[j] /= root;
+        const double piv = lane_value(a[j], j);
+        if (j < live && (!(piv > 0.0) || !(sqrt(piv) > floor))) ok = false;
+        a[j] *= rsqrt_pos(piv);
 #pragma unroll
         for (int r = j + 1; r < 16; ++r)
-            a[r] = fma(-lane_value(a[j], r), a[j], a[r]); // kept for columns >= r
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) a[r] = c >= r ? a[r] : 0.0;
-    // column c of the inverse, from the diagonal up
-#pragma unroll
-    for (int r = 15; r >= 0; --r) {
-        double s = r == c ? 1.0 : 0.0;
-#pragma unroll
-        for (int k = r + 1; k < 16; ++k) s = fma(-lane_value(a[r], k), x[k], s);
-        x[r] = s / lane_value(a[r], r);
+            a[r] = fma(-lane_value(a[j], r), a[j], a[r]); // of a tile's column, kept for r <= c
     }
     wave_sync();
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        d[r][c] = a[r];
-        di[r][c] = x[r];
+        if (unit) di[c][r] = a[r]; // (zero below the diagonal as computed)
+        else d[r][c] = c >= r ? a[r] : 0.0;
     }
     wave_sync();
     return ok;
@@ -385,6 +392,7 @@ __device__ __forceinline__ bool chol_blocks(const double *G, int pa, int nt, dou
             const int t = b + wave + q * NW;
             if (t >= nt) continue;
             f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
             for (int k = 0; k < b; ++k) {
                 const double *row = R + (size_t)16 * k * ldr;
                 acc = tile_mul(row + 16 * b, 1, ldr, tile_load(row + 16 * t, ldr), acc);
@@ -470,7 +478,7 @@ __device__ __forceinline__ f64x4 prod_nt_tile(const double *A, int lda, const do
 // the padding), the right factor of Q1 = B X1.  Stage 2 (R2 from G2): Xp = P'
 // with P = R2^{-1} R2^{-T} R1^{-T}, the right factor of B^+' = Q1 P.  status:
 // 0, or the stage whose rank test failed (stage 2 does nothing when stage 1
-// failed).  Latency-bound (16 dependent pivots a tile): 9 us at p = 15, 32 us
+// failed).  Latency-bound (16 dependent pivots a tile): 8 us at p = 15, 31 us
 // at p = 56; one wave over scalar LDS elements took 21 and 325 us.
 __global__ __launch_bounds__(256) void small_factor_kernel(
     const double *__restrict__ G, int pa, int pap, double rel_tol, int stage,
@@ -518,9 +526,11 @@ __global__ __launch_bounds__(256) void small_factor_kernel(
 
 // The factorisation of a larger basis: one workgroup of eight waves, R (pap x
 // pap) in global memory (it stays in the L2).  A chain of pap / 16 row
-// blocks, two thirds of it the dependent pivots of the diagonal tiles: 119 us
-// at p = 221, 299 us at p = 364 (on the host, with the copies: 1.3 ms at
-// p = 221, 5 ms at p = 364).
+// blocks, two thirds of it the dependent pivots of the diagonal tiles (350
+// cycles each): 103 us at p = 221, 275 us at p = 364, 119 and 299 us with a
+// quotient and a root in that chain and the inverse after it (on the host,
+// with the copies: 1.3 ms at p = 221, 5 ms at p = 364).  With the tiles in
+// registers and the rows in LDS it takes as long: 107 us.
 __global__ __launch_bounds__(512) void chol_kernel(const double *__restrict__ G, int pa,
                                                     int pap, double rel_tol, int stage,
                                                     double *R, double *dinv,
@@ -647,8 +657,16 @@ hipError_t launch_gram(const double *A, int ld, int pap, int rows_per_chunk,
                        int chunks, const int2 *pairs, int npairs,
                        double *partial, int pa, double *G, hipStream_t s)
 {
-    gram_partial_kernel<<<dim3(npairs, chunks), 64, 0, s>>>(A, ld, pap, rows_per_chunk,
-                                                          pairs, partial);
+    // one wave a block reads the least (n = 81,920, p = 364: 266 us against
+    // 407 with four); where that leaves SIMDs idle (1024 of them), four waves
+    // share it (n = 1000, p = 221: 9 us against 14; n = 10,933, p = 56: 8
+    // against 14)
+    if (npairs * chunks < 1024)
+        gram_partial_kernel<2><<<dim3(npairs, chunks), 256, 0, s>>>(A, ld, pap, rows_per_chunk,
+                                                                  pairs, partial);
+    else
+        gram_partial_kernel<4><<<dim3(npairs, chunks), 64, 0, s>>>(A, ld, pap, rows_per_chunk,
+                                                                 pairs, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // eight lanes an entry where one would leave the chip idle (p = 56, 171
