@@ -9,6 +9,7 @@
 //   channel_kernel  alpha^{k+1} = alpha^k + beta and the channel table
 //                   Gamma[l][c] = (D_c alpha^{k+1})_l of u, d_t u, grad u and
 //                   the upper-triangular hessian, in FP64 and FP32.
+//   small_update_kernel  the three of them for a small problem.
 #include "bsde_common.h"
 
 #include <hip/hip_runtime.h>
@@ -18,10 +19,10 @@ namespace bsde {
 // c_i and sample variance from the per-workgroup sums (fixed order in g)
 // the groups' means and sums of squared deviations combined in group order;
 // group g holds the paths g ppg .. (g + 1) ppg - 1 below M
-__device__ __forceinline__ void finalize_point(const double *__restrict__ partial,
-                                               int i, int groups, int M, int ppg,
-                                               double *__restrict__ c,
-                                               double *__restrict__ var)
+__device__ __forceinline__ double finalize_point(const double *__restrict__ partial,
+                                                 int i, int groups, int M, int ppg,
+                                                 double *__restrict__ c,
+                                                 double *__restrict__ var)
 {
     double n = 0.0, mean = 0.0, m2 = 0.0;
     for (int g = 0; g < groups; ++g) {
@@ -32,6 +33,7 @@ __device__ __forceinline__ void finalize_point(const double *__restrict__ partia
     }
     c[i] = mean;
     var[i] = M > 1 ? m2 / (M - 1) : 0.0;
+    return mean;
 }
 
 __global__ void finalize_kernel(const double *__restrict__ partial, int n,
@@ -102,6 +104,76 @@ __global__ __launch_bounds__(256) void channel_kernel(
 {
     channel_entries(alpha_in, beta, alpha_out, rowptr, cols, vals, p, nnz, blockIdx.x,
                     g64, g32);
+}
+
+// The three of them for a small problem by one workgroup of 16 waves: c goes
+// through LDS, a wave takes every 16th row of W with the four partial sums of
+// project_row's four waves (so the sums are the same), and the table follows
+// the coefficients.  Three launches of a few workgroups each cost their
+// latencies one after the other and, below a path kernel of some 20 us, more
+// time on the host than on the GPU: n = 512, p = 15 takes 11 us an iteration
+// outside the path kernel instead of 17 to 21 (10 instead of 12 where the
+// path kernel is longer).
+constexpr int kSmallN = 4096;
+__global__ __launch_bounds__(1024) void small_update_kernel(
+    const double *__restrict__ partial, int n, int groups, int M, int ppg,
+    double *__restrict__ c, double *__restrict__ var, const double *__restrict__ W,
+    const double *__restrict__ alpha_in, double *__restrict__ alpha_out,
+    const int *__restrict__ rowptr, const int *__restrict__ cols,
+    const double *__restrict__ vals, int p, int nnz, double *__restrict__ g64,
+    float *__restrict__ g32)
+{
+    __shared__ double cs[kSmallN], a[kMaxP];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // what does not wait for c: the start of the wave's first row, and where
+    // this lane's first entry of the table begins and ends
+    double w0[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        w0[q] = wave < p && lane + 64 * q < n ? W[(size_t)wave * n + lane + 64 * q] : 0.0;
+    int k0 = 0, k1 = 0;
+    if ((int)threadIdx.x < nnz) {
+        k0 = rowptr[threadIdx.x];
+        k1 = rowptr[threadIdx.x + 1];
+    }
+    for (int i = threadIdx.x; i < n; i += 1024)
+        cs[i] = finalize_point(partial, i, groups, M, ppg, c, var);
+    __syncthreads();
+    for (int l = wave; l < p; l += 16) {
+        const double *w = W + (size_t)l * n;
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        int i = lane;
+        if (l == wave) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (lane + 64 * q < n) acc[q & 3] += w0[q] * cs[lane + 64 * q];
+            i += 512;
+        }
+#pragma unroll 2
+        for (; i < n; i += 256)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (i + 64 * q < n) acc[q] += w[i + 64 * q] * cs[i + 64 * q];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) acc[q] += __shfl_xor(acc[q], off);
+        if (lane == 0) {
+            a[l] = alpha_in[l] + ((acc[0] + acc[1]) + (acc[2] + acc[3]));
+            alpha_out[l] = a[l];
+        }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < nnz; e += 1024) {
+        if (e >= 1024) {
+            k0 = rowptr[e];
+            k1 = rowptr[e + 1];
+        }
+        double v = 0.0;
+        for (int k = k0; k < k1; ++k) v += vals[k] * a[cols[k]];
+        g64[e] = v;
+        g32[e] = (float)v;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -358,6 +430,16 @@ hipError_t launch_update(int n, int groups, int M, int ppg, int p, int nnz,
                          const int *rowptr, const int *cols, const double *vals,
                          double *g64, float *g32, hipEvent_t *ev /* 3 events or NULL */)
 {
+    // one workgroup reads all the moments and W: up to 4096 groups of paths
+    // and 32 K entries it is the faster way (n = 800, p = 35: 15 us an
+    // iteration outside the path kernel against 20; n = 1296, p = 35: 18.7
+    // against 17.0; with 16,384 groups at n = 2048, p = 15: 21 against 14)
+    if (!ev && p <= kMaxP && (long)n * groups <= kSmallN && (long)n * p <= 32768) {
+        hipLaunchKernelGGL(small_update_kernel, dim3(1), dim3(1024), 0, s, partial, n, groups, M,
+                           ppg, c, var, W, alpha_in, alpha_out, rowptr, cols, vals, p, nnz, g64,
+                           g32);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(finalize_kernel, dim3((n + 255) / 256), dim3(256), 0,
                        s, partial, n, groups, M, ppg, c, var);
     if (ev) (void)hipEventRecord(ev[0], s);

@@ -74,3 +74,25 @@ def test_moments_do_not_depend_on_the_tiling(M, tilings, prec):
         scale = 1.0 + abs(rc) + np.sqrt(rv) + abs(y[i])
         assert abs(c0[i] - rc) <= TOL[prec] * scale
         assert abs(v0[i] - rv) <= 4 * TOL[prec] * scale ** 2
+
+
+# points, functions, tilings and table entries around the sizes of the
+# one-workgroup update (16 waves, strides of 512 and 1024, 32 K entries)
+@pytest.mark.parametrize("d,n_t,n_x,eta,M,tiling", [
+    (1, 3, 3, 2, 40, None), (1, 9, 57, 4, 300, None), (1, 9, 57, 8, 2500, (7, 2)),
+    (1, 16, 128, 4, 500, (2, 1)), (1, 16, 128, 4, 600, (3, 1)), (2, 6, 11, 4, 300, None),
+    (2, 8, 16, 5, 70, None), (5, 8, 60, 3, 90, None), (10, 4, 70, 2, 40, None)])
+def test_update_in_one_workgroup_and_in_three_launches(d, n_t, n_x, eta, M, tiling):
+    cfg = _config(d, M, 4, "fp64", n_t=n_t, n_x=n_x, eta=eta)
+    print("update d=%d n_t=%d n_x=%d eta=%d M=%d" % (d, n_t, n_x, eta, M), flush=True)
+    got = []
+    for level in (1, 2):  # level 2 times the three kernels
+        with bsde.Problem(cfg) as P:
+            P.set_timing(level)
+            if tiling:
+                P.set_tiling(*tiling)
+            P.solve()
+            got.append((P.coefficients(),) + P.corrections(1))
+    # the same sums in the same order
+    for x, y in zip(*got):
+        assert np.all(np.abs(x - y) <= 1e-13 * np.max(np.abs(y)))
