@@ -63,7 +63,8 @@ hipError_t launch_gemm_ax(const double *A, int ld, const double *X, int pap, boo
                           int ncols, hipStream_t s, const int *skip);
 size_t factor_workspace(int pap);
 hipError_t launch_factor(const double *G, int pa, int pap, double rel_tol, int stage,
-                         double *X1, double *Xp, double *work, int *status, hipStream_t s);
+                         double *X1, double *Xp, double *work, int *status, bool beside,
+                         hipStream_t s);
 hipError_t launch_project(const double *W, const double *c, int n, int p, double *beta,
                           hipStream_t s);
 bool kernel_op_exists(int d, int vol);
@@ -621,12 +622,12 @@ public:
         if (e == hipSuccess) e = pool_alloc((void **)&dSmall_, n_small);
         if (e == hipSuccess)
             e = hipMemcpyAsync(dSmall_, stage_, n_small, hipMemcpyHostToDevice, s);
-        if (e == hipSuccess && pa_ < h_->p)
-            e = hipMemsetAsync(h_->d_W, 0, sizeof(double) * (size_t)h_->p * h_->n, s);
         return e;
     }
 
-    hipError_t enqueue(hipStream_t s, int *status)
+    // of the points pts into W, whose rows of inactive multi-indices it leaves
+    // (the caller has made them zero); beside: a path kernel fills the GPU meanwhile
+    hipError_t enqueue(hipStream_t s, int *status, const double *pts, double *W, bool beside)
     {
         const int n = h_->n;
         const size_t sq = (size_t)pap_ * pap_;
@@ -634,20 +635,20 @@ public:
         const double *dMS = (const double *)(dSmall_ + o_ms_);
         const int2 *dPairs = (const int2 *)(dSmall_ + o_pairs_);
         int *dStatus = (int *)(dSmall_ + o_status_);
-        hipError_t e = launch_basis_matrix(h_->d_pts, n, ld_, h_->d + 1, (const int8_t *)dSmall_,
+        hipError_t e = launch_basis_matrix(pts, n, ld_, h_->d + 1, (const int8_t *)dSmall_,
                                            pa_, pap_, h_->eta, dMS, dMS + kMaxD, h_->base.T, dB_,
                                            s);
         if (e == hipSuccess)
             e = launch_gram(dB_, ld_, pap_, rpc_, chunks_, dPairs, npairs_, dPart_, pa_, dG_, s);
         // a failed rank test leaves its status, and the later steps do nothing
-        if (e == hipSuccess) e = launch_factor(dG_, pa_, pap_, 1e-7, 1, dX1, dX, dWork, dStatus, s);
+        if (e == hipSuccess) e = launch_factor(dG_, pa_, pap_, 1e-7, 1, dX1, dX, dWork, dStatus, beside, s);
         if (e == hipSuccess)
             e = launch_gemm_ax(dB_, ld_, dX1, pap_, true, dQ_, ld_, ld_, nullptr, pap_, s, dStatus);
         if (e == hipSuccess)
             e = launch_gram(dQ_, ld_, pap_, rpc_, chunks_, dPairs, npairs_, dPart_, pa_, dG_, s);
-        if (e == hipSuccess) e = launch_factor(dG_, pa_, pap_, 1e-3, 2, dX1, dX, dWork, dStatus, s);
+        if (e == hipSuccess) e = launch_factor(dG_, pa_, pap_, 1e-3, 2, dX1, dX, dWork, dStatus, beside, s);
         if (e == hipSuccess)
-            e = launch_gemm_ax(dQ_, ld_, dX, pap_, false, h_->d_W, n, n,
+            e = launch_gemm_ax(dQ_, ld_, dX, pap_, false, W, n, n,
                                (const int *)(dSmall_ + o_map_), pa_, s, dStatus);
         if (e == hipSuccess)
             e = hipMemcpyAsync(status, dStatus, sizeof(int), hipMemcpyDeviceToHost, s);
@@ -668,57 +669,111 @@ private:
 constexpr const char *kRankMessage = "basis matrix is numerically rank deficient on the grid";
 } // namespace
 
-// The redrawn points of one solve on stream s (Algorithm 1): draw(h, k) sends
-// iteration k's points up from one of two pinned slots and forms their
-// pseudo-inverse, all stream-ordered, so that the host draws the next
-// iteration's points while the GPU works; full_rank looks at the rank tests
-// once s is synchronized.
+// The redrawn points of one solve on stream s (Algorithm 1).  An iteration's
+// points and their pseudo-inverse do not depend on the iterate, and the
+// set-up is a chain of small kernels: it runs on a stream of the library's own
+// while the iteration before it runs on s, into the other of two sets of
+// buffers, the problem's own and one of the solve's (one set, and everything
+// on s, when that cannot be allocated or the paths are few).  Time outside
+// the path kernel an iteration: 0.30 -> 0.03 ms at d = 10, n = 1000, p = 221,
+// M = 30 000; 0.59 -> 0.06 at n = 1800, p = 364; 0.13 -> 0.08 at d = 5, p = 84,
+// where the kernels wait for room beside the path kernel.  draw(k) sends iteration k's points up from one
+// of two pinned slots and enqueues their pseudo-inverse, begin(k) makes s wait
+// for them and gives their set, end(k) frees it; finish() brings the last
+// iteration's points and pseudo-inverse into the problem's own buffers, and
+// full_rank() looks at the rank tests once s is synchronized.
 namespace {
 class RedrawWork {
 public:
-    explicit RedrawWork(hipStream_t s) : s_(s) {}
+    struct Set {
+        double *pts, *W;
+    };
+    RedrawWork(bsde_problem_s *h, hipStream_t s) : h_(h), s_(s), set_{{h->d_pts, h->d_W}, {}} {}
     RedrawWork(const RedrawWork &) = delete;
     RedrawWork &operator=(const RedrawWork &) = delete;
     ~RedrawWork()
     {
         if (!pinv_) return;
-        (void)hipStreamSynchronize(s_); // also after an error: the buffers go back
+        // also after an error: the buffers go back
+        if (side_) {
+            (void)hipStreamSynchronize(side_);
+            setup_stream_put(side_);
+        }
+        (void)hipStreamSynchronize(s_);
+        if (!finished_) h_->pts_k = -1; // the points on the device are not known
         for (Slot &q : slot_) {
             pinned_put(q.mem, q.cap);
             if (q.sent) event_put(q.sent);
         }
+        for (hipEvent_t ev : {ready_[0], ready_[1], used_[0], used_[1]})
+            if (ev) event_put(ev);
+        pool_free(set_[1].pts);
+        pool_free(set_[1].W);
         pinned_put(pinned_status_, status_cap_);
     }
 
-    hipError_t draw(bsde_problem_s *h, int k)
+    // after: an event on s before which the buffers may be in use
+    hipError_t draw(int k, hipEvent_t after)
     {
-        const size_t bytes = sizeof(double) * h->pts.size();
+        const size_t bytes = sizeof(double) * h_->pts.size();
         hipError_t e = hipSuccess;
-        if (!pinv_) {
-            pinv_.reset(new PseudoInverse(h));
-            status_.assign((size_t)h->K_it, 0);
-            for (Slot &q : slot_) {
-                // (too large to pin: the points then go up from h->pts)
-                if (bytes <= kPinnedMax) q.mem = pinned_get(bytes, &q.cap);
-                if ((e = event_get(&q.sent)) != hipSuccess) return e;
-            }
-            if ((e = pinv_->init(s_)) != hipSuccess) return e;
-            pinned_status_ = (int *)pinned_get(sizeof(int) * status_.size(), &status_cap_);
-        }
+        if (!pinv_) init_error_ = init(bytes, after);
+        if (init_error_ != hipSuccess) return init_error_;
+        const hipStream_t ws = side_ ? side_ : s_;
+        const int t = target(k);
         Slot &q = slot_[count_ & 1];
-        if (!q.mem) e = hipStreamSynchronize(s_); // h->pts is still being read
+        if (!q.mem) e = hipStreamSynchronize(ws); // h->pts is still being read
         else if (count_ >= 2) e = hipEventSynchronize(q.sent);
         if (e != hipSuccess) return e;
-        make_points(h, k, h->pts);
-        if (q.mem) std::memcpy(q.mem, h->pts.data(), bytes);
-        e = hipMemcpyAsync(h->d_pts, q.mem ? q.mem : (void *)h->pts.data(), bytes,
-                           hipMemcpyHostToDevice, s_);
-        if (e == hipSuccess) e = hipEventRecord(q.sent, s_);
-        if (e == hipSuccess) e = pinv_->enqueue(s_, status() + count_);
+        make_points(h_, k, h_->pts);
+        if (q.mem) std::memcpy(q.mem, h_->pts.data(), bytes);
+        if (side_ && in_use_[t]) e = hipStreamWaitEvent(side_, used_[t], 0);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(set_[t].pts, q.mem ? q.mem : (void *)h_->pts.data(), bytes,
+                               hipMemcpyHostToDevice, ws);
+        if (e == hipSuccess) e = hipEventRecord(q.sent, ws);
+        if (e == hipSuccess)
+            e = pinv_->enqueue(ws, status() + count_, set_[t].pts, set_[t].W, side_ && long_path_);
+        if (e == hipSuccess && side_) e = hipEventRecord(ready_[t], side_);
         if (e != hipSuccess) return e;
         ++count_;
-        h->pts_k = k;
+        h_->pts_k = drawn_ = k;
         return hipSuccess;
+    }
+    // whether iteration k's points have been drawn here
+    bool drawn(int k) const { return count_ > 0 && drawn_ >= k; }
+    // whether draw(k) may run before end(k - 1) (after an error it reports it)
+    bool ahead(hipEvent_t after)
+    {
+        if (!pinv_) init_error_ = init(sizeof(double) * h_->pts.size(), after);
+        return side_ != nullptr || init_error_ != hipSuccess;
+    }
+
+    hipError_t begin(int k, Set &set)
+    {
+        const int t = target(k);
+        set = set_[t];
+        return side_ && drawn(k) ? hipStreamWaitEvent(s_, ready_[t], 0) : hipSuccess;
+    }
+    hipError_t end(int k)
+    {
+        last_ = k;
+        if (!side_) return hipSuccess;
+        in_use_[target(k)] = true;
+        return hipEventRecord(used_[target(k)], s_);
+    }
+    hipError_t finish()
+    {
+        hipError_t e = hipSuccess;
+        if (pinv_ && target(last_) == 1) {
+            e = hipMemcpyAsync(h_->d_pts, set_[1].pts, sizeof(double) * h_->pts.size(),
+                               hipMemcpyDeviceToDevice, s_);
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(h_->d_W, set_[1].W, sizeof(double) * (size_t)h_->p * h_->n,
+                                   hipMemcpyDeviceToDevice, s_);
+        }
+        finished_ = e == hipSuccess;
+        return e;
     }
 
     bool full_rank()
@@ -729,19 +784,62 @@ public:
     }
 
 private:
+    hipError_t init(size_t bytes, hipEvent_t after)
+    {
+        pinv_.reset(new PseudoInverse(h_));
+        status_.assign((size_t)h_->K_it, 0);
+        hipError_t e = hipSuccess;
+        for (Slot &q : slot_) {
+            // (too large to pin: the points then go up from h->pts)
+            if (bytes <= kPinnedMax) q.mem = pinned_get(bytes, &q.cap);
+            if ((e = event_get(&q.sent)) != hipSuccess) return e;
+        }
+        first_ = h_->k_done;
+        // The second stream's events cost some 10 us an iteration: not below
+        // 2e7 asset steps, a path kernel of 40 us (d = 3, n = 300, M = 1000,
+        // N = 5: 0.38 ms without, 0.45 with it; d = 5, n = 1000: 1.06 and
+        // 1.01).  From 1e9 on the path kernel (0.6 ms and more) outlasts the
+        // set-up, whose kernels are then those that fit beside it.
+        const double steps = (double)h_->n * h_->M * h_->base.N * h_->d;
+        long_path_ = steps > 1e9;
+        const size_t w_bytes = sizeof(double) * (size_t)h_->p * h_->n;
+        bool two = steps > 2e7 &&
+                   pool_alloc((void **)&set_[1].pts, bytes) == hipSuccess &&
+                   pool_alloc((void **)&set_[1].W, w_bytes) == hipSuccess;
+        for (hipEvent_t *ev : {&ready_[0], &ready_[1], &used_[0], &used_[1]})
+            two = two && event_get(ev) == hipSuccess;
+        if (two && setup_stream_get(&side_) != hipSuccess) side_ = nullptr;
+        if (steps > 2e7 && !side_) (void)hipGetLastError(); // one set does
+        if (side_) {
+            if ((e = hipStreamWaitEvent(side_, after, 0)) != hipSuccess) return e;
+            if (h_->act.size() < (size_t)h_->p)
+                e = hipMemsetAsync(set_[1].W, 0, w_bytes, side_);
+        }
+        if (e == hipSuccess) e = pinv_->init(side_ ? side_ : s_);
+        if (e != hipSuccess) return e;
+        pinned_status_ = (int *)pinned_get(sizeof(int) * status_.size(), &status_cap_);
+        return hipSuccess;
+    }
+    // the set of iteration k: the problem's own first
+    int target(int k) const { return side_ ? (k - first_) & 1 : 0; }
     int *status() { return pinned_status_ ? pinned_status_ : status_.data(); }
     struct Slot {
         void *mem = nullptr;
         size_t cap = 0;
         hipEvent_t sent = nullptr;
     };
-    hipStream_t s_;
+    bsde_problem_s *h_;
+    hipStream_t s_, side_ = nullptr;
     std::unique_ptr<PseudoInverse> pinv_;
+    Set set_[2];
+    hipEvent_t ready_[2] = {nullptr, nullptr}, used_[2] = {nullptr, nullptr};
+    bool in_use_[2] = {false, false}, finished_ = false, long_path_ = false;
+    hipError_t init_error_ = hipSuccess;
     Slot slot_[2];
     int *pinned_status_ = nullptr;
     std::vector<int> status_;
     size_t status_cap_ = 0;
-    int count_ = 0;
+    int count_ = 0, first_ = 0, drawn_ = -1, last_ = 0;
 };
 } // namespace
 
@@ -750,7 +848,9 @@ static bsde_status device_pseudo_inverse(const bsde_problem_s *h, hipStream_t s)
 {
     PseudoInverse pinv(h);
     hipError_t e = pinv.init(s);
-    if (e == hipSuccess) e = pinv.enqueue(s, pinv.own_status());
+    if (e == hipSuccess && h->act.size() < (size_t)h->p) // rows that stay zero
+        e = hipMemsetAsync(h->d_W, 0, sizeof(double) * (size_t)h->p * h->n, s);
+    if (e == hipSuccess) e = pinv.enqueue(s, pinv.own_status(), h->d_pts, h->d_W, false);
     const hipError_t se = hipStreamSynchronize(s);
     if (e == hipSuccess) e = se;
     if (e != hipSuccess)
@@ -1313,14 +1413,16 @@ static bsde_status prepare_tiling(bsde_problem h, int &groups, int &ppl,
 
 // the Monte Carlo path kernel of h's operator (least squares: the channel
 // table; kernel operator: the point table)
+// at the points pts
 static hipError_t launch_problem_path(const bsde_problem_s *h, int blocks, hipStream_t s,
-                                      const PathParams &prm, hipEvent_t ev0, hipEvent_t ev1)
+                                      const PathParams &prm, const double *pts,
+                                      hipEvent_t ev0, hipEvent_t ev1)
 {
     const bool fp32 = h->precision == BSDE_FP32_PATHS;
     if (h->kop)
-        return launch_kernel_path(h->d, fp32, blocks, s, prm, h->d_pts, h->d_ktab,
+        return launch_kernel_path(h->d, fp32, blocks, s, prm, pts, h->d_ktab,
                                   h->d_partial, ev0, ev1);
-    return launch_path(h->d, h->eta, h->q10, fp32, blocks, s, prm, h->d_pts,
+    return launch_path(h->d, h->eta, h->q10, fp32, blocks, s, prm, pts,
                        fp32 ? (const void *)h->d_g32 : (const void *)h->d_g64,
                        h->d_partial, ev0, ev1);
 }
@@ -1346,7 +1448,7 @@ bsde_status bsde_solve(bsde_problem h, void *hip_stream)
         std::vector<hipEvent_t> &v;
         ~Release() { for (auto &x : v) event_put(x); }
     } release_events{ev};
-    RedrawWork redraw(s);
+    RedrawWork redraw(h, s);
     HIP_TRY(hipEventRecord(ev[0], s));
     // channel table of the starting coefficients (the kernel operator's
     // table already holds the current point values)
@@ -1356,24 +1458,29 @@ bsde_status bsde_solve(bsde_problem h, void *hip_stream)
     for (int it = 0; it < iters; ++it) {
         const int k = h->k_done + it;
         hipEvent_t *e = per ? &ev[2 + (size_t)per * it] : nullptr;
-        if (h->redraw && h->pts_k != k) {
-            // Algorithm 1: new points for this iteration, and the
-            // pseudo-inverse of their basis matrix (stream-ordered after the
-            // previous iteration's use of the old ones)
-            const hipError_t re = redraw.draw(h, k);
-            if (re != hipSuccess) {
-                h->pts_k = -1; // the points on the device are not known
-                return fail(re == hipErrorOutOfMemory ? BSDE_ENOMEM : BSDE_EDEVICE,
-                            std::string("redrawn points: ") + hipGetErrorString(re));
-            }
+        // Algorithm 1: new points for this iteration, and the pseudo-inverse
+        // of their basis matrix
+        auto draw = [&](int kk) {
+            const hipError_t re = redraw.draw(kk, ev[0]);
+            if (re == hipSuccess) return BSDE_OK;
+            h->pts_k = -1; // the points on the device are not known
+            return fail(re == hipErrorOutOfMemory ? BSDE_ENOMEM : BSDE_EDEVICE,
+                        std::string("redrawn points: ") + hipGetErrorString(re));
+        };
+        RedrawWork::Set set{h->d_pts, h->d_W};
+        if (h->redraw) {
+            if (!redraw.drawn(k) && h->pts_k != k && (st = draw(k)) != BSDE_OK) return st;
+            HIP_TRY(redraw.begin(k, set));
         }
         PathParams prm = h->base;
         prm.k = (uint32_t)k;
         prm.groups = groups;
         prm.paths_per_lane = ppl;
         prm.n = h->n;
-        HIP_TRY(launch_problem_path(h, h->n * groups, s, prm, e ? e[0] : nullptr,
+        HIP_TRY(launch_problem_path(h, h->n * groups, s, prm, set.pts, e ? e[0] : nullptr,
                                     e ? e[1] : nullptr));
+        if (h->redraw && it + 1 < iters && redraw.ahead(ev[0]) && (st = draw(k + 1)) != BSDE_OK)
+            return st;
         if (h->kop) {
             // c^k, then y^k = u^k(points) + c^k with u^k = h[y^{k-1}]
             // (alpha row k; row 0 = 0 is u^0 = 0) into row k + 1 and the table
@@ -1393,12 +1500,14 @@ bsde_status bsde_solve(bsde_problem h, void *hip_stream)
         }
         HIP_TRY(launch_update(h->n, groups, h->M, kBlock * ppl, h->p, h->n_live, s,
                               h->d_partial, h->d_c + (size_t)k * h->n,
-                              h->d_var + (size_t)k * h->n, h->d_W, h->d_beta,
+                              h->d_var + (size_t)k * h->n, set.W, h->d_beta,
                               h->d_alpha + (size_t)k * h->p,
                               h->d_alpha + (size_t)(k + 1) * h->p, h->d_rowptr, h->d_cols,
                               h->d_vals, h->d_g64, h->d_g32,
-                              per == 5 ? e + 2 : nullptr)); // records e[2..4] // records e[2..4]
+                              per == 5 ? e + 2 : nullptr)); // records e[2..4]
+        if (h->redraw) HIP_TRY(redraw.end(k));
     }
+    if (h->redraw) HIP_TRY(redraw.finish());
     HIP_TRY(hipEventRecord(ev[1], s));
     // the coefficients come back with the end of the solve, one wait for both
     const size_t alpha_bytes = sizeof(double) * h->alpha_hist.size();
@@ -1922,7 +2031,7 @@ bsde_status bsde_autotune(bsde_problem h, void *hip_stream, int *groups_out,
         prm.n = h->n;
         double t_min = 1e300;
         for (int rep = 0; rep < 5; ++rep) { // first launch warms up
-            HIP_TRY(launch_problem_path(h, h->n * c.first, s, prm, e0, e1));
+            HIP_TRY(launch_problem_path(h, h->n * c.first, s, prm, h->d_pts, e0, e1));
             HIP_TRY(hipEventSynchronize(e1));
             float ms = 0.f;
             (void)hipEventElapsedTime(&ms, e0, e1);

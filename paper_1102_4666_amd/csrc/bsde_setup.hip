@@ -392,7 +392,7 @@ __device__ __forceinline__ bool chol_blocks(const double *G, int pa, int nt, dou
             const int t = b + wave + q * NW;
             if (t >= nt) continue;
             f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
+#pragma unroll (TW > 4 ? 2 : 4)
             for (int k = 0; k < b; ++k) {
                 const double *row = R + (size_t)16 * k * ldr;
                 acc = tile_mul(row + 16 * b, 1, ldr, tile_load(row + 16 * t, ldr), acc);
@@ -531,13 +531,17 @@ __global__ __launch_bounds__(256) void small_factor_kernel(
 // quotient and a root in that chain and the inverse after it (on the host,
 // with the copies: 1.3 ms at p = 221, 5 ms at p = 364).  With the tiles in
 // registers and the rows in LDS it takes as long: 107 us.
-__global__ __launch_bounds__(512) void chol_kernel(const double *__restrict__ G, int pa,
-                                                    int pap, double rel_tol, int stage,
-                                                    double *R, double *dinv,
-                                                    int *__restrict__ status)
+// Beside a path kernel that fills the GPU it takes four waves of at most 168
+// registers: a workgroup that needs more of a compute unit than one of the
+// path kernel's leaves when it ends would wait for the last of them.
+template <int NW>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void chol_kernel(
+    const double *__restrict__ G, int pa, int pap, double rel_tol, int stage, double *R,
+    double *dinv, int *__restrict__ status)
 {
     if (stage == 2 && *status != 0) return;
-    const bool ok = chol_blocks<8, (kFactorTiles + 7) / 8>(G, pa, pap >> 4, rel_tol, R, pap, dinv);
+    const bool ok = chol_blocks<NW, (kFactorTiles + NW - 1) / NW>(G, pa, pap >> 4, rel_tol, R, pap,
+                                                                  dinv);
     if (threadIdx.x == 0) *status = ok ? 0 : stage;
 }
 
@@ -617,9 +621,11 @@ size_t factor_workspace(int pap)
 }
 
 // One stage of the factorisation from the Gram matrix G (pa x pa): stage 1
-// writes X1 = R1^{-1}, stage 2 Xp = P' (both pap x pap)
+// writes X1 = R1^{-1}, stage 2 Xp = P' (both pap x pap).  beside: other kernels
+// fill the GPU meanwhile
 hipError_t launch_factor(const double *G, int pa, int pap, double rel_tol, int stage,
-                         double *X1, double *Xp, double *work, int *status, hipStream_t s)
+                         double *X1, double *Xp, double *work, int *status, bool beside,
+                         hipStream_t s)
 {
     const int nt = pap >> 4;
     if (pa < 1 || pap != pad16(pa) || nt > kFactorTiles || (stage != 1 && stage != 2))
@@ -630,7 +636,10 @@ hipError_t launch_factor(const double *G, int pa, int pap, double rel_tol, int s
     }
     const size_t sq = (size_t)pap * pap;
     double *R = work, *Y = work + sq, *T2 = work + 2 * sq, *dinv = work + 3 * sq;
-    chol_kernel<<<1, 512, 0, s>>>(G, pa, pap, rel_tol, stage, R, dinv, status);
+    if (beside)
+        chol_kernel<4><<<1, 256, 0, s>>>(G, pa, pap, rel_tol, stage, R, dinv, status);
+    else
+        chol_kernel<8><<<1, 512, 0, s>>>(G, pa, pap, rel_tol, stage, R, dinv, status);
     tri_inv_kernel<<<nt, 256, (nt + 4) * 256 * sizeof(double), s>>>(R, pa, pap, dinv,
                                                                   stage == 1 ? X1 : Y, status);
     if (stage == 2) {
