@@ -916,21 +916,21 @@ TuneKey tune_key(const bsde_problem_s *h)
 
 static void auto_tiling(const bsde_problem_s *h, int &groups, int &ppl)
 {
-    // Up to 16 384 tiles, as few groups as leave each ppl blocks of paths.
-    // 1024 workgroups run at a time in the FP32 d = 1 kernel, and rounds of
-    // long tiles end with idle units: n = 2048, M = 4000 takes 0.280 ms in
-    // 2048 tiles, 0.250 in 16 384, 0.262 in 32 768, which pay for their starts
-    // and reductions (d = 10, q = 0.6, n = 1000, M = 30 000: 3.00, 2.80,
-    // 2.92 ms).  From n = 8193 on one group is as fast as several (d = 2,
-    // n = 16 384, M = 2000: 1.895 ms against 1.907 in two).
+    // Up to 16 384 tiles of two blocks of paths or more, and single blocks up
+    // to 2048 tiles.  1024 workgroups run at a time in the FP32 d = 1 kernel,
+    // and rounds of long tiles end with idle units: n = 2048, M = 4000 takes
+    // 0.280 ms in 2048 tiles, 0.250 in 16 384, 0.262 in 32 768 of one block
+    // (d = 10, q = 0.6, n = 1000, M = 30 000: 3.00, 2.80, 2.92 ms).  A tile of
+    // one block pays for its start and reduction as much as a longer one:
+    // alone that is the same (n = 2048, M = 1000: 0.077 ms in tiles of one and
+    // of two), but a batch, which has tiles enough, loses by it (eight
+    // problems, M = 550: 8.8 ms in single blocks, 7.0 in tiles of three).
+    // From n = 8193 on one group is as fast as several (d = 2, n = 16 384,
+    // M = 2000: 1.895 ms against 1.907 in two).
     const int blocks = (h->M + kBlock - 1) / kBlock;
-    const int want = std::max(1, std::min(blocks, 16384 / h->n));
+    const int fill = (2048 + h->n - 1) / h->n, most = std::min(16384 / h->n, blocks / 2);
+    const int want = std::max(1, std::min(blocks, std::max(fill, most)));
     ppl = (blocks + want - 1) / want;
-    // two blocks a tile rather than one where they divide M evenly and still
-    // make 4096 tiles (n = 2048, M = 2000: 0.1348 ms against 0.1351, and in
-    // FP64, d = 2, 0.562 against 0.572; a batch of seven problems, whose
-    // others fill the GPU, 3% faster)
-    if (ppl == 1 && blocks % 2 == 0 && (long)h->n * (blocks / 2) >= 4096) ppl = 2;
     groups = (blocks + ppl - 1) / ppl;
 }
 
