@@ -8,7 +8,9 @@ functions), M = 1000 paths, N = 50 Euler steps, 10 Picard iterations) with
 FP64 paths, sums and update: problem set-up (grid, basis matrix, device
 least-squares factorisation, upload), every Picard iteration on the GPU
 (paths, driver, reductions, least-squares update), the price/delta query
-and tear-down.  `value` is Euler path-steps per second of whole jobs.
+and tear-down.  `value` is Euler path-steps per second of whole jobs, of the
+steps the paths take: those of the points at T (a tenth of them here) have
+none and are not counted.
 
 The one JSON line also carries:
   roofline      of the dominant kernel (the Monte Carlo path kernel of the
@@ -186,14 +188,14 @@ ISSUE_CYCLES_D1_FP32 = {
 # hash is recorded with it and for the tiling it was taken at; otherwise
 # the line reports null.
 TRAFFIC = [
-    {"sources_sha16": "ea70fccb41332a0b", "tiling": [1, 4],
-     "fetch_kib": 14090.0, "write_kib": 934600.0,
+    {"sources_sha16": "6dc45edbe372c17a", "tiling": [1, 4],
+     "fetch_kib": 11850.0, "write_kib": 246400.0,
      "profile": "profiles/path_kernel_d5_fp64_geo_basket_d5.md"},
-    {"sources_sha16": "ea70fccb41332a0b", "tiling": [4, 1],
-     "fetch_kib": 24310.0, "write_kib": 3686000.0,
+    {"sources_sha16": "6dc45edbe372c17a", "tiling": [4, 1],
+     "fetch_kib": 23370.0, "write_kib": 897500.0,
      "profile": "profiles/path_kernel_d5_fp64_geo_basket_d5.md"},
-    {"sources_sha16": "ea70fccb41332a0b", "tiling": [2, 2],
-     "fetch_kib": 17950.0, "write_kib": 1832000.0,
+    {"sources_sha16": "6dc45edbe372c17a", "tiling": [2, 2],
+     "fetch_kib": 15690.0, "write_kib": 478300.0,
      "profile": "profiles/path_kernel_d5_fp64_geo_basket_d5.md"},
 ]
 # Counter-derived figures of the same kernel (same profiles, same guard):
@@ -201,17 +203,17 @@ TRAFFIC = [
 # busy = SQ_VALU_MFMA_BUSY_CYCLES / 1024 SIMDs / cycles, FP64 vector FLOP
 # issued = 64 (2 FMA + MUL + ADD + TRANS) instructions per launch.
 COUNTERS = [
-    {"sources_sha16": "ea70fccb41332a0b", "tiling": [1, 4],
-     "valu_issue": 0.907, "mfma_busy": 0.0,
-     "fp64_vector_flop_per_launch": 7.45e11, "fp64_matrix_flop_per_launch": 0.0,
+    {"sources_sha16": "6dc45edbe372c17a", "tiling": [1, 4],
+     "valu_issue": 0.901, "mfma_busy": 0.0,
+     "fp64_vector_flop_per_launch": 5.04e11, "fp64_matrix_flop_per_launch": 0.0,
      "profile": "profiles/path_kernel_d5_fp64_geo_basket_d5.md"},
-    {"sources_sha16": "ea70fccb41332a0b", "tiling": [4, 1],
-     "valu_issue": 0.909, "mfma_busy": 0.0,
-     "fp64_vector_flop_per_launch": 7.57e11, "fp64_matrix_flop_per_launch": 0.0,
+    {"sources_sha16": "6dc45edbe372c17a", "tiling": [4, 1],
+     "valu_issue": 0.896, "mfma_busy": 0.0,
+     "fp64_vector_flop_per_launch": 5.11e11, "fp64_matrix_flop_per_launch": 0.0,
      "profile": "profiles/path_kernel_d5_fp64_geo_basket_d5.md"},
-    {"sources_sha16": "ea70fccb41332a0b", "tiling": [2, 2],
-     "valu_issue": 0.909, "mfma_busy": 0.0,
-     "fp64_vector_flop_per_launch": 7.49e11, "fp64_matrix_flop_per_launch": 0.0,
+    {"sources_sha16": "6dc45edbe372c17a", "tiling": [2, 2],
+     "valu_issue": 0.899, "mfma_busy": 0.0,
+     "fp64_vector_flop_per_launch": 5.07e11, "fp64_matrix_flop_per_launch": 0.0,
      "profile": "profiles/path_kernel_d5_fp64_geo_basket_d5.md"},
 ]
 FETCH_FACTOR, WRITE_FACTOR = 2.0, 1.0
@@ -280,8 +282,14 @@ HEADLINE_NAME = ("d=5 American geometric-basket put, penalised BSDE (penalty 1),
 FORCED_TILING = None
 
 
+def stepped_points(cfg, n):
+    """Points whose paths take Euler steps: all but those of a tensor or
+    random grid's last time node, which are at T."""
+    return n if cfg.get("grid") == "uniform" else n - n // cfg["n_t"]
+
+
 def steps_of(cfg, n):
-    return n * cfg["M"] * cfg["N"] * cfg["K_it"]
+    return stepped_points(cfg, n) * cfg["M"] * cfg["N"] * cfg["K_it"]
 
 
 def run_job(cfg, stream, phases=None):
@@ -348,7 +356,7 @@ def roofline(cfg, n, path_ms, tiling, precision):
     p, live = live_channel_entries(d, cfg["eta"], cfg.get("q", 1.0))
     fl, fl_mfma = flop_per_path_step(d, p, C, live, cfg["N"], cfg.get("vol_kind", "bump"),
                                      cfg.get("payoff", "put"))
-    launch_steps = n * cfg["M"] * cfg["N"]
+    launch_steps = stepped_points(cfg, n) * cfg["M"] * cfg["N"]
     t = path_ms * 1e-3
     achieved = fl * launch_steps / t
     peak = FP64_VECTOR_PEAK if precision == "fp64" else FP32_VECTOR_PEAK
@@ -440,7 +448,7 @@ def batched_vs_fp64(stream, reps=2):
                 P.solve(stream)
         torch.cuda.synchronize()
         dt = time.perf_counter() - t0
-        steps = sum(P.n * P.cfg["M"] * P.cfg["N"] * P.cfg["K_it"] for P in probs)
+        steps = sum(steps_of(P.cfg, P.n) for P in probs)
         res = {}
         for nm, P in zip(names, probs):
             price, delta = P.price_delta()
@@ -486,7 +494,7 @@ def d1_leg(steps, stream):
     import workloads
     cfg = workloads.amer_put_d1(omega=1.0, precision="fp32")
     r = timed_jobs(cfg, steps, 1, stream)
-    launch_steps = r["n"] * cfg["M"] * cfg["N"]
+    launch_steps = stepped_points(cfg, r["n"]) * cfg["M"] * cfg["N"]
     cyc = sum(ISSUE_CYCLES_D1_FP32.values()) * launch_steps / 64
     t = r["path_ms"] * 1e-3
     return {"workload": "d=1 American put, penalty 1, bump local vol, 128x16 "
@@ -702,7 +710,7 @@ def single_launches(names, euler_steps=None, precision="fp32", overrides=None):
                 P.set_tiling(*FORCED_TILING)
             P.solve()
             out[nm] = {"path_kernel_ms": P.timings()[0],
-                       "path_steps": P.n * cfg["M"] * cfg["N"]}
+                       "path_steps": stepped_points(cfg, P.n) * cfg["M"] * cfg["N"]}
             if cfg.get("kernel_bw", 0.0) > 0.0:
                 out[nm]["kernel_pairs"] = P.n * cfg["M"] * P.n
     return out

@@ -581,6 +581,20 @@ __host__ __device__ inline void combine_moments(double &n, double &mean, double 
     n = nt;
 }
 
+// Segments of points the projection W c is split into, one workgroup a row and
+// segment (p of them alone leave the GPU's 256 compute units idle or unevenly
+// loaded), and the points of a segment
+__host__ __device__ inline int project_segments(int n)
+{
+    const int s = (n + 4095) / 4096;
+    return s < 32 ? s : 32;
+}
+__host__ __device__ inline int segment_points(int n)
+{
+    const int s = project_segments(n);
+    return ((n + s - 1) / s + 255) & ~255;
+}
+
 // One problem of the batched reduction / update kernels (one iteration).
 struct BatchUpdateDesc {
     const double *partial; // n x groups x 2: mean and M2 of each group's paths
@@ -589,7 +603,7 @@ struct BatchUpdateDesc {
     int nnz;               // entries of the packed channel table
     double *c, *var;       // this iteration's slices
     const double *W;       // p x n pseudo-inverse
-    double *beta;          // p
+    double *beta;          // project_segments(n) x p
     const double *alpha_in;
     double *alpha_out;
     const int *rowptr;     // the channel update (sparse rows of the packed table)

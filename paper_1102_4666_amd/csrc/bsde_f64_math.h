@@ -31,6 +31,11 @@
 // The radius takes the square root from the hardware reciprocal square
 // root and Newton steps (sqrt_nonneg).
 //
+// The path kernels take the logarithm, sine, cosine and powers of two from
+// tables (Tables below), each of these series cut short by the table's share
+// of the argument; the series by themselves are the tables' yardstick in the
+// tests.
+//
 // Plain double and 32-bit integer arithmetic (and the hardware reciprocal
 // and reciprocal-square-root seeds on the device), so the same code also
 // compiles for the host: the test suite checks it there against

@@ -1246,7 +1246,8 @@ bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
                  o_ktab = o_col + al256(b_col), n_block = o_ktab + al256(b_ktab);
     bool ok = dalloc(&h->d_block, n_block) &&
               (kop || dalloc((void **)&h->d_W, sizeof(double) * (size_t)h->p * h->n)) &&
-              dalloc((void **)&h->d_beta, sizeof(double) * h->p) &&
+              dalloc((void **)&h->d_beta,
+                     sizeof(double) * h->p * (size_t)project_segments(h->n)) &&
               dalloc((void **)&h->d_c, sizeof(double) * (size_t)h->K_it * h->n) &&
               dalloc((void **)&h->d_var, sizeof(double) * (size_t)h->K_it * h->n);
     if (!ok) {
@@ -1904,7 +1905,7 @@ size_t bsde::problem_device_bytes(int d, const bsde_grid *grid, int M, int K_it)
                          al256((size_t)(K_it + 1) * p * 8) + al256(entries * 8) +
                          al256(entries * 4) + al256((entries + 1) * 4) +
                          al256(nonzeros * 4);
-    const size_t sizes[] = {block, (size_t)p * n * 8, (size_t)p * 8,
+    const size_t sizes[] = {block, (size_t)p * n * 8, (size_t)p * 8 * project_segments((int)n),
                             (size_t)K_it * n * 8,
                             (size_t)K_it * n * 8,
                             n * groups * 16};
@@ -2221,16 +2222,18 @@ bsde_status bsde_fit_values(bsde_problem h, const double *y, int k_done)
     if (h->kop) return fail(BSDE_EUNSUPPORTED, "the kernel operator fits no basis");
     // alpha = R^{-1} Q' y = W y on the device (0.10 ms with its copies
     // at n = 10933, p = 56; W copied back and multiplied on the host: 0.60 ms)
-    const size_t y_bytes = sizeof(double) * (size_t)h->n, a_bytes = sizeof(double) * (size_t)h->p;
+    const int segs = project_segments(h->n);
+    const size_t y_bytes = sizeof(double) * (size_t)h->n;
     double *dy = nullptr;
     hipStream_t us = nullptr;
-    std::vector<double> a(h->p, 0.0);
+    std::vector<double> a((size_t)segs * h->p, 0.0);
     hipError_t e = pool_alloc((void **)&dy, y_bytes);
     if (e == hipSuccess) e = setup_stream_get(&us);
     if (e == hipSuccess) e = hipMemcpyAsync(dy, y, y_bytes, hipMemcpyHostToDevice, us);
     if (e == hipSuccess) e = launch_project(h->d_W, dy, h->n, h->p, h->d_beta, us);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(a.data(), h->d_beta, a_bytes, hipMemcpyDeviceToHost, us);
+        e = hipMemcpyAsync(a.data(), h->d_beta, sizeof(double) * a.size(), hipMemcpyDeviceToHost,
+                           us);
     if (us) {
         const hipError_t se = hipStreamSynchronize(us);
         if (e == hipSuccess) e = se;
@@ -2240,6 +2243,8 @@ bsde_status bsde_fit_values(bsde_problem h, const double *y, int k_done)
     if (e != hipSuccess)
         return fail(e == hipErrorOutOfMemory ? BSDE_ENOMEM : BSDE_EDEVICE,
                     std::string("fit: ") + hipGetErrorString(e));
+    for (int q = 1; q < segs; ++q)
+        for (int l = 0; l < h->p; ++l) a[l] += a[(size_t)q * h->p + l];
     return store_alpha(h, a.data(), k_done);
 }
 

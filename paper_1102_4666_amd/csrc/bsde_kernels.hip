@@ -44,29 +44,34 @@ __global__ void finalize_kernel(const double *__restrict__ partial, int n,
     if (i < n) finalize_point(partial, i, groups, M, ppg, c, var);
 }
 
-// beta_l = sum_i W[l][i] c_i (W = R^{-1} Q', row-major p x n): lanes
-// strided over i, fixed-order tree reduction; one workgroup of 256 lanes
+// beta[seg][l] = sum_i W[l][i] c_i over the points of the segment (W = R^{-1}
+// Q', row-major p x n; the channel update adds the segments in order): lanes
+// strided over i, fixed-order tree reduction; one workgroup of 256 lanes.
+// Bound by reading W: n = 81 920, p = 364 (238 MB) 36 us, n = 40 960, p = 84
+// (27 MB) 7 us; with one workgroup a row 85 to 125 and 41.
 __device__ __forceinline__ void project_row(const double *__restrict__ W,
                                             const double *__restrict__ c,
-                                            int n, int l,
+                                            int n, int p, int l, int seg,
                                             double *__restrict__ beta)
 {
     const double *w = W + (size_t)l * n;
+    const int len = segment_points(n), end = min(n, (seg + 1) * len);
     double acc = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) acc += w[i] * c[i];
+    for (int i = seg * len + threadIdx.x; i < end; i += 256) acc += w[i] * c[i];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
     __shared__ double red[4];
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) beta[l] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (threadIdx.x == 0)
+        beta[(size_t)seg * p + l] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 __global__ __launch_bounds__(256) void project_kernel(
     const double *__restrict__ W, const double *__restrict__ c, int n,
     double *__restrict__ beta)
 {
-    project_row(W, c, n, blockIdx.x, beta);
+    project_row(W, c, n, gridDim.x, blockIdx.x, blockIdx.y, beta);
 }
 
 constexpr int kMaxP = 512;
@@ -77,14 +82,19 @@ constexpr int kMaxP = 512;
 // D_c alpha (channel 0, the first p entries, is a itself and also stores a
 // as the next coefficients).  FP64 and FP32 copies.
 __device__ __forceinline__ void channel_entries(
-    const double *__restrict__ alpha_in, const double *__restrict__ beta,
+    const double *__restrict__ alpha_in, const double *__restrict__ beta, int segs,
     double *__restrict__ alpha_out, const int *__restrict__ rowptr,
     const int *__restrict__ cols, const double *__restrict__ vals, int p,
     int nnz, int blk, double *__restrict__ g64, float *__restrict__ g32)
 {
     __shared__ double a[kMaxP];
-    for (int m = threadIdx.x; m < p; m += 256)
-        a[m] = alpha_in[m] + (beta ? beta[m] : 0.0);
+    for (int m = threadIdx.x; m < p; m += 256) {
+        double b = 0.0;
+        if (beta)
+#pragma unroll 8
+            for (int q = 0; q < segs; ++q) b += beta[(size_t)q * p + m];
+        a[m] = alpha_in[m] + b;
+    }
     __syncthreads();
     const int e = blk * 256 + (int)threadIdx.x;
     if (e >= nnz) return;
@@ -97,12 +107,12 @@ __device__ __forceinline__ void channel_entries(
 
 // 256 entries per workgroup
 __global__ __launch_bounds__(256) void channel_kernel(
-    const double *__restrict__ alpha_in, const double *__restrict__ beta,
+    const double *__restrict__ alpha_in, const double *__restrict__ beta, int segs,
     double *__restrict__ alpha_out, const int *__restrict__ rowptr,
     const int *__restrict__ cols, const double *__restrict__ vals, int p, int nnz,
     double *__restrict__ g64, float *__restrict__ g32)
 {
-    channel_entries(alpha_in, beta, alpha_out, rowptr, cols, vals, p, nnz, blockIdx.x,
+    channel_entries(alpha_in, beta, segs, alpha_out, rowptr, cols, vals, p, nnz, blockIdx.x,
                     g64, g32);
 }
 
@@ -191,7 +201,8 @@ __global__ __launch_bounds__(256) void batch_project_kernel(
     const BatchUpdateDesc *__restrict__ d)
 {
     const BatchUpdateDesc &q = d[blockIdx.y];
-    if ((int)blockIdx.x < q.p) project_row(q.W, q.c, q.n, blockIdx.x, q.beta);
+    if ((int)blockIdx.x < q.p && (int)blockIdx.z < project_segments(q.n))
+        project_row(q.W, q.c, q.n, q.p, blockIdx.x, blockIdx.z, q.beta);
 }
 
 __global__ __launch_bounds__(256) void batch_channel_kernel(
@@ -199,7 +210,7 @@ __global__ __launch_bounds__(256) void batch_channel_kernel(
 {
     const BatchUpdateDesc &q = d[blockIdx.y];
     if ((int)blockIdx.x * 256 < q.nnz)
-        channel_entries(q.alpha_in, with_beta ? q.beta : nullptr,
+        channel_entries(q.alpha_in, with_beta ? q.beta : nullptr, project_segments(q.n),
                         with_beta ? q.alpha_out : nullptr, q.rowptr, q.cols, q.vals,
                         q.p, q.nnz, blockIdx.x, q.g64, q.g32);
 }
@@ -285,8 +296,8 @@ hipError_t launch_batch_update(int nprob, int max_n, int max_p, int max_cb,
 {
     hipLaunchKernelGGL(batch_finalize_kernel,
                        dim3((max_n + 255) / 256, nprob), dim3(256), 0, s, d);
-    hipLaunchKernelGGL(batch_project_kernel, dim3(max_p, nprob), dim3(256), 0,
-                       s, d);
+    hipLaunchKernelGGL(batch_project_kernel, dim3(max_p, nprob, project_segments(max_n)),
+                       dim3(256), 0, s, d);
     hipLaunchKernelGGL(batch_channel_kernel, dim3(max_cb, nprob), dim3(256), 0,
                        s, d, 1);
     return hipGetLastError();
@@ -443,11 +454,12 @@ hipError_t launch_update(int n, int groups, int M, int ppg, int p, int nnz,
     hipLaunchKernelGGL(finalize_kernel, dim3((n + 255) / 256), dim3(256), 0,
                        s, partial, n, groups, M, ppg, c, var);
     if (ev) (void)hipEventRecord(ev[0], s);
-    hipLaunchKernelGGL(project_kernel, dim3(p), dim3(256), 0, s, W, c, n,
+    hipLaunchKernelGGL(project_kernel, dim3(p, project_segments(n)), dim3(256), 0, s, W, c, n,
                        beta);
     if (ev) (void)hipEventRecord(ev[1], s);
     hipLaunchKernelGGL(channel_kernel, dim3((nnz + 255) / 256), dim3(256), 0, s,
-                       alpha_in, beta, alpha_out, rowptr, cols, vals, p, nnz, g64, g32);
+                       alpha_in, beta, project_segments(n), alpha_out, rowptr, cols, vals, p,
+                       nnz, g64, g32);
     if (ev) (void)hipEventRecord(ev[2], s);
     return hipGetLastError();
 }
@@ -455,7 +467,8 @@ hipError_t launch_update(int n, int groups, int M, int ppg, int p, int nnz,
 hipError_t launch_project(const double *W, const double *c, int n, int p, double *beta,
                           hipStream_t s)
 {
-    hipLaunchKernelGGL(project_kernel, dim3(p), dim3(256), 0, s, W, c, n, beta);
+    hipLaunchKernelGGL(project_kernel, dim3(p, project_segments(n)), dim3(256), 0, s, W, c, n,
+                       beta);
     return hipGetLastError();
 }
 
@@ -464,7 +477,7 @@ hipError_t launch_channels(int p, int nnz, hipStream_t s, const double *alpha,
                            double *g64, float *g32)
 {
     hipLaunchKernelGGL(channel_kernel, dim3((nnz + 255) / 256), dim3(256), 0, s,
-                       alpha, (const double *)nullptr, (double *)nullptr, rowptr,
+                       alpha, (const double *)nullptr, 0, (double *)nullptr, rowptr,
                        cols, vals, p, nnz, g64, g32);
     return hipGetLastError();
 }

@@ -27,7 +27,8 @@ static __shared__ f64::Tables f64_tables;
 
 // ---------------------------------------------------------------------------
 // Precision-specific arithmetic.  FP32: hardware transcendentals (v_log_f32
-// is log2, v_sin/v_cos take revolutions); FP64: the device math library.
+// is log2, v_sin/v_cos take revolutions); FP64: bsde_f64_math.h in the
+// step loop, the device math library outside it.
 // ---------------------------------------------------------------------------
 template <typename Real>
 struct Arith;
@@ -1194,14 +1195,15 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
 
 // Waves per SIMD the register allocation must allow.  The d = 10 (FP32)
 // and d = 5 (FP32 and FP64) kernels are held to three waves (168 registers
-// a lane): left to themselves they take 180-240 and run at two, and at
-// three they run 10-17% faster (d = 10 serving shape, d = 5 FP64), with
-// what does not fit (up to 340 bytes a lane) stored and reloaded once per
-// path, outside the Euler loop.  At four waves (128 registers) the FP64
-// d = 5 kernel spills inside the Euler loop and takes 60% longer, and the
-// FP32 d = 10 one gains 2%.  d = 10 in FP64 runs at two waves.  d = 2 in
-// FP64 (eta = 5 wants over 256 registers) runs at two waves, 29% faster than
-// at one.
+// a lane): left to themselves those of d = 5 in FP64 and of d = 10 with the
+// channel table take 180-240 and run at two, and at three they run 10-17%
+// faster, with what does not fit (up to 340 bytes a lane) stored and reloaded
+// once per path, outside the Euler loop.  (In the cubic form FP32 takes 85 at
+// d = 5, five waves, and 149 to 168 at d = 10.)  At four waves (128
+// registers) the FP64 d = 5 kernel spills inside the Euler loop and takes 60%
+// longer, and the FP32 d = 10 one gains 2%.  d = 10 in FP64 runs at two
+// waves.  d = 2 in FP64 (eta = 5 wants over 256 registers) runs at two waves,
+// 29% faster than at one.
 template <int D, typename Real>
 constexpr int min_waves()
 {
@@ -1211,8 +1213,8 @@ constexpr int min_waves()
     return 1;
 }
 
-// One problem: workgroup b runs tile (i, g) = (b / groups, b % groups) and
-// writes its sums to partial[2 b].
+// One problem: workgroup b runs a tile (i, g) of point i = b / groups and
+// writes its moments to partial[2 (i groups + g)].
 template <int D, int ETA, typename Real, int VOL, int Q, int OP = kOpBasis>
 __global__ __launch_bounds__(kBlock, (min_waves<D, Real>())) void path_kernel(
     const PathParams prm, const double *__restrict__ pts,

@@ -96,3 +96,17 @@ def test_update_in_one_workgroup_and_in_three_launches(d, n_t, n_x, eta, M, tili
     # the same sums in the same order
     for x, y in zip(*got):
         assert np.all(np.abs(x - y) <= 1e-13 * np.max(np.abs(y)))
+
+
+# points around one segment of the projection, several, and the most of them
+@pytest.mark.parametrize("n_t,n_x", [(16, 256), (17, 241), (9, 911), (7, 19000)])
+def test_fit_over_segments_of_points(n_t, n_x):
+    cfg = _config(1, 1, 1, "fp64", n_t=n_t, n_x=n_x, eta=2)
+    print("segments n_t=%d n_x=%d" % (n_t, n_x), flush=True)
+    with bsde.Problem(cfg) as P:
+        S = P.points()
+        P.fit_values(1.0 + S[:, 0] * S[:, 1] - 0.3 * S[:, 1] ** 2, 1)
+        t, x = S[::97, 0], S[::97, 1:]
+        price, _ = P.price_delta(t, np.exp(x))
+    ref = 1.0 + t * x[:, 0] - 0.3 * x[:, 0] ** 2
+    assert np.all(np.abs(price - ref) <= 1e-10 * np.max(np.abs(ref)))
