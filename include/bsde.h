@@ -175,9 +175,9 @@ bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
  * update, eq. alpha) on the given HIP stream (hipStream_t, NULL = the
  * default stream) and returns once they are complete.  Starting
  * coefficients are u^0 = 0 unless set with bsde_set_coefficients or
- * bsde_fit_values.  With redraw, each iteration first draws its points
- * and factorises their basis matrix on the device (waiting for the
- * previous iteration).  Errors: BSDE_EDEVICE, BSDE_ERANK (redrawn points
+ * bsde_fit_values.  With redraw, each iteration's points are drawn and
+ * their basis matrix is factorised on the device, beside the previous
+ * iteration where that pays.  Errors: BSDE_EDEVICE, BSDE_ERANK (redrawn points
  * with a rank-deficient basis matrix). */
 bsde_status bsde_solve(bsde_problem h, void *hip_stream);
 
@@ -380,9 +380,8 @@ typedef struct {
 bsde_status bsde_server_create(size_t hbm_budget_bytes, int max_inflight,
                                int setup_threads, bsde_server *out);
 /* Queues a request (arrays are copied); ticket receives its id.  Errors:
- * BSDE_EINVAL, BSDE_EUNSUPPORTED (a grid with redraw: such problems need
- * a host-side factorisation between iterations and run through bsde_solve
- * only); errors of the problem itself arrive through bsde_server_poll. */
+ * BSDE_EINVAL, BSDE_EUNSUPPORTED (a grid with redraw: such problems are
+ * factorised anew at every iteration and run through bsde_solve only); errors of the problem itself arrive through bsde_server_poll. */
 bsde_status bsde_server_submit(bsde_server s, const bsde_request *req,
                                unsigned long long *ticket);
 /* Result of a ticket; with wait = 0 returns BSDE_EBUSY while it runs.  A
