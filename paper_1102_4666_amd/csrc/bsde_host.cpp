@@ -57,7 +57,7 @@ hipError_t launch_basis_matrix(const double *pts, int n, int ld, int dp,
                                double T, double *B, hipStream_t s);
 hipError_t launch_gram(const double *A, int ld, int pap, int rows_per_chunk,
                        int chunks, const int2 *pairs, int npairs,
-                       double *partial, int pa, double *G, hipStream_t s);
+                       double *partial, int pa, double *G, bool beside, hipStream_t s);
 hipError_t launch_gemm_ax(const double *A, int ld, const double *X, int pap, bool upper,
                           double *Y, int ldy, int nrows, const int *colmap,
                           int ncols, hipStream_t s, const int *skip);
@@ -639,13 +639,13 @@ public:
                                            pa_, pap_, h_->eta, dMS, dMS + kMaxD, h_->base.T, dB_,
                                            s);
         if (e == hipSuccess)
-            e = launch_gram(dB_, ld_, pap_, rpc_, chunks_, dPairs, npairs_, dPart_, pa_, dG_, s);
+            e = launch_gram(dB_, ld_, pap_, rpc_, chunks_, dPairs, npairs_, dPart_, pa_, dG_, beside, s);
         // a failed rank test leaves its status, and the later steps do nothing
         if (e == hipSuccess) e = launch_factor(dG_, pa_, pap_, 1e-7, 1, dX1, dX, dWork, dStatus, beside, s);
         if (e == hipSuccess)
             e = launch_gemm_ax(dB_, ld_, dX1, pap_, true, dQ_, ld_, ld_, nullptr, pap_, s, dStatus);
         if (e == hipSuccess)
-            e = launch_gram(dQ_, ld_, pap_, rpc_, chunks_, dPairs, npairs_, dPart_, pa_, dG_, s);
+            e = launch_gram(dQ_, ld_, pap_, rpc_, chunks_, dPairs, npairs_, dPart_, pa_, dG_, beside, s);
         if (e == hipSuccess) e = launch_factor(dG_, pa_, pap_, 1e-3, 2, dX1, dX, dWork, dStatus, beside, s);
         if (e == hipSuccess)
             e = launch_gemm_ax(dQ_, ld_, dX, pap_, false, W, n, n,
@@ -676,12 +676,13 @@ constexpr const char *kRankMessage = "basis matrix is numerically rank deficient
 // buffers, the problem's own and one of the solve's (one set, and everything
 // on s, when that cannot be allocated or the paths are few).  Time outside
 // the path kernel an iteration: 0.30 -> 0.03 ms at d = 10, n = 1000, p = 221,
-// M = 30 000; 0.59 -> 0.06 at n = 1800, p = 364; 0.13 -> 0.08 at d = 5, p = 84,
-// where the kernels wait for room beside the path kernel.  draw(k) sends iteration k's points up from one
-// of two pinned slots and enqueues their pseudo-inverse, begin(k) makes s wait
-// for them and gives their set, end(k) frees it; finish() brings the last
-// iteration's points and pseudo-inverse into the problem's own buffers, and
-// full_rank() looks at the rank tests once s is synchronized.
+// M = 30 000; 0.59 -> 0.05 at n = 1800, p = 364; 0.13 -> 0.03 at d = 5, p = 84; in
+// FP64 at d = 10, whose path kernel leaves no registers free, 0.60 -> 0.50.
+// draw(k) sends iteration k's points up from one of two pinned slots and
+// enqueues their pseudo-inverse, begin(k) makes s wait for them and gives their
+// set, end(k) frees it; finish() brings the last iteration's points and
+// pseudo-inverse into the problem's own buffers, and full_rank() looks at the
+// rank tests once s is synchronized.
 namespace {
 class RedrawWork {
 public:
@@ -742,7 +743,8 @@ public:
     }
     // whether iteration k's points have been drawn here
     bool drawn(int k) const { return count_ > 0 && drawn_ >= k; }
-    // whether draw(k) may run before end(k - 1) (after an error it reports it)
+    // whether the next draw may run beside the present iteration (after an
+    // error it reports it); before the iteration's end, which it makes count
     bool ahead(hipEvent_t after)
     {
         if (!pinv_) init_error_ = init(sizeof(double) * h_->pts.size(), after);
@@ -1480,8 +1482,6 @@ bsde_status bsde_solve(bsde_problem h, void *hip_stream)
         prm.n = h->n;
         HIP_TRY(launch_problem_path(h, h->n * groups, s, prm, set.pts, e ? e[0] : nullptr,
                                     e ? e[1] : nullptr));
-        if (h->redraw && it + 1 < iters && redraw.ahead(ev[0]) && (st = draw(k + 1)) != BSDE_OK)
-            return st;
         if (h->kop) {
             // c^k, then y^k = u^k(points) + c^k with u^k = h[y^{k-1}]
             // (alpha row k; row 0 = 0 is u^0 = 0) into row k + 1 and the table
@@ -1506,7 +1506,11 @@ bsde_status bsde_solve(bsde_problem h, void *hip_stream)
                               h->d_alpha + (size_t)(k + 1) * h->p, h->d_rowptr, h->d_cols,
                               h->d_vals, h->d_g64, h->d_g32,
                               per == 5 ? e + 2 : nullptr)); // records e[2..4]
-        if (h->redraw) HIP_TRY(redraw.end(k));
+        if (h->redraw) {
+            const bool ahead = it + 1 < iters && redraw.ahead(ev[0]);
+            HIP_TRY(redraw.end(k));
+            if (ahead && (st = draw(k + 1)) != BSDE_OK) return st;
+        }
     }
     if (h->redraw) HIP_TRY(redraw.finish());
     HIP_TRY(hipEventRecord(ev[1], s));

@@ -89,20 +89,21 @@ __global__ __launch_bounds__(256) void basis_matrix_kernel(
 // (bi, bj), bi <= bj, of A'A over the rows of its chunk, a wave Q x Q tiles of
 // 16 x 16 of it.  A chunk of 64 rows is one batch of loads, so that its time
 // is their latency once and not four times (n = 1000, p = 221: 23 -> 9 us;
-// n = 81,920, p = 364: 365 -> 266 us).
+// n = 81,920, p = 364: 365 -> 266 us).  SINGLE: a wave is a workgroup of its own
+// (blockIdx.z).
 // The rows assigned to the four k-slots of an MFMA are permuted so that
 // each lane reads 4 consecutive rows of one column (32 contiguous bytes,
 // a whole 128-byte line per 4 lanes): in step t of a 16-row group at s,
 // k-slot kk takes row s + 4 kk + t, the same for both operands.
 // partial[chunk][r][c] holds the block's entries (r in bi's rows).
-template <int Q>
-__global__ __launch_bounds__(64 * (4 / Q) * (4 / Q)) void gram_partial_kernel(
+template <int Q, bool SINGLE = false>
+__global__ __launch_bounds__(SINGLE ? 64 : 64 * (4 / Q) * (4 / Q)) void gram_partial_kernel(
     const double *__restrict__ A, int ld, int pap, int rows_per_chunk,
     const int2 *__restrict__ pairs, double *__restrict__ partial)
 {
     const int2 pr = pairs[blockIdx.x];
     const int chunk = blockIdx.y;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = SINGLE ? blockIdx.z : threadIdx.x >> 6;
     // the wave's tiles of the block: Q x Q from (qa, qb)
     const int qa = 4 * pr.x + Q * (wave / (4 / Q)), qb = 4 * pr.y + Q * (wave % (4 / Q));
     const int r0 = chunk * rows_per_chunk;
@@ -531,18 +532,29 @@ __global__ __launch_bounds__(256) void small_factor_kernel(
 // quotient and a root in that chain and the inverse after it (on the host,
 // with the copies: 1.3 ms at p = 221, 5 ms at p = 364).  With the tiles in
 // registers and the rows in LDS it takes as long: 107 us.
-// Beside a path kernel that fills the GPU it takes four waves of at most 168
-// registers: a workgroup that needs more of a compute unit than one of the
-// path kernel's leaves when it ends would wait for the last of them.
 template <int NW>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void chol_kernel(
-    const double *__restrict__ G, int pa, int pap, double rel_tol, int stage, double *R,
-    double *dinv, int *__restrict__ status)
+__device__ __forceinline__ void chol_workgroup(const double *G, int pa, int pap, double rel_tol,
+                                               int stage, double *R, double *dinv, int *status)
 {
     if (stage == 2 && *status != 0) return;
     const bool ok = chol_blocks<NW, (kFactorTiles + NW - 1) / NW>(G, pa, pap >> 4, rel_tol, R, pap,
                                                                   dinv);
     if (threadIdx.x == 0) *status = ok ? 0 : stage;
+}
+__global__ __launch_bounds__(512) void chol_kernel(const double *__restrict__ G, int pa, int pap,
+                                                   double rel_tol, int stage, double *R,
+                                                   double *dinv, int *__restrict__ status)
+{
+    chol_workgroup<8>(G, pa, pap, rel_tol, stage, R, dinv, status);
+}
+// Beside a path kernel that fills the GPU: four waves of at most 168 registers.
+// A workgroup that needs more of a compute unit than one of the path kernel's
+// leaves when it ends would wait for the last of them.
+__global__ __launch_bounds__(256, 3) void chol_beside_kernel(
+    const double *__restrict__ G, int pa, int pap, double rel_tol, int stage, double *R,
+    double *dinv, int *__restrict__ status)
+{
+    chol_workgroup<4>(G, pa, pap, rel_tol, stage, R, dinv, status);
 }
 
 // X = R^{-1} (pap x pap, zero below the diagonal and in the padding): a
@@ -637,9 +649,9 @@ hipError_t launch_factor(const double *G, int pa, int pap, double rel_tol, int s
     const size_t sq = (size_t)pap * pap;
     double *R = work, *Y = work + sq, *T2 = work + 2 * sq, *dinv = work + 3 * sq;
     if (beside)
-        chol_kernel<4><<<1, 256, 0, s>>>(G, pa, pap, rel_tol, stage, R, dinv, status);
+        chol_beside_kernel<<<1, 256, 0, s>>>(G, pa, pap, rel_tol, stage, R, dinv, status);
     else
-        chol_kernel<8><<<1, 512, 0, s>>>(G, pa, pap, rel_tol, stage, R, dinv, status);
+        chol_kernel<<<1, 512, 0, s>>>(G, pa, pap, rel_tol, stage, R, dinv, status);
     tri_inv_kernel<<<nt, 256, (nt + 4) * 256 * sizeof(double), s>>>(R, pa, pap, dinv,
                                                                   stage == 1 ? X1 : Y, status);
     if (stage == 2) {
@@ -664,13 +676,19 @@ hipError_t launch_basis_matrix(const double *pts, int n, int ld, int dp,
 
 hipError_t launch_gram(const double *A, int ld, int pap, int rows_per_chunk,
                        int chunks, const int2 *pairs, int npairs,
-                       double *partial, int pa, double *G, hipStream_t s)
+                       double *partial, int pa, double *G, bool beside, hipStream_t s)
 {
-    // one wave a block reads the least (n = 81,920, p = 364: 266 us against
+    // Beside a path kernel, single waves of one tile (42 registers) find room
+    // in what its waves leave free; workgroups of four waves of 120 waited for
+    // its end (d = 5, p = 84: 67 us an iteration against 1550).
+    // Otherwise one wave a block reads the least (n = 81,920, p = 364: 266 us against
     // 407 with four); where that leaves SIMDs idle (1024 of them), four waves
     // share it (n = 1000, p = 221: 9 us against 14; n = 10,933, p = 56: 8
     // against 14)
-    if (npairs * chunks < 1024)
+    if (beside)
+        gram_partial_kernel<1, true><<<dim3(npairs, chunks, 16), 64, 0, s>>>(
+            A, ld, pap, rows_per_chunk, pairs, partial);
+    else if (npairs * chunks < 1024)
         gram_partial_kernel<2><<<dim3(npairs, chunks), 256, 0, s>>>(A, ld, pap, rows_per_chunk,
                                                                   pairs, partial);
     else
