@@ -178,7 +178,8 @@ bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
  * bsde_fit_values.  With redraw, each iteration's points are drawn and
  * their basis matrix is factorised on the device, beside the previous
  * iteration where that pays.  Errors: BSDE_EDEVICE, BSDE_ERANK (redrawn points
- * with a rank-deficient basis matrix). */
+ * with a rank-deficient basis matrix: no iteration counts as done, and the
+ * points are those of the last one before the deficient draw). */
 bsde_status bsde_solve(bsde_problem h, void *hip_stream);
 
 /* Price u(t, log S) and dollar deltas Delta_j = e^{-x_j} d_{x_j} u (the

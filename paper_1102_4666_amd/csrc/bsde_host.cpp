@@ -681,15 +681,22 @@ constexpr const char *kRankMessage = "basis matrix is numerically rank deficient
 // draw(k) sends iteration k's points up from one of two pinned slots and
 // enqueues their pseudo-inverse, begin(k) makes s wait for them and gives their
 // set, end(k) frees it; finish() brings the last iteration's points and
-// pseudo-inverse into the problem's own buffers, and full_rank() looks at the
-// rank tests once s is synchronized.
+// pseudo-inverse into the problem's own buffers.  The rank tests are looked at
+// without a wait: failed() knows those of the draws that have ended when
+// draw() reuses their slot, so that a solve stops two iterations after a
+// deficient one, and full_rank() all of them once s is synchronized.  After a
+// failure restore() leaves the problem with the points and pseudo-inverse of
+// the iteration before the deficient one, the last that ran.
 namespace {
 class RedrawWork {
 public:
     struct Set {
         double *pts, *W;
     };
-    RedrawWork(bsde_problem_s *h, hipStream_t s) : h_(h), s_(s), set_{{h->d_pts, h->d_W}, {}} {}
+    RedrawWork(bsde_problem_s *h, hipStream_t s)
+        : h_(h), s_(s), set_{{h->d_pts, h->d_W}, {}}, from_(h->pts_k)
+    {
+    }
     RedrawWork(const RedrawWork &) = delete;
     RedrawWork &operator=(const RedrawWork &) = delete;
     ~RedrawWork()
@@ -701,7 +708,7 @@ public:
             setup_stream_put(side_);
         }
         (void)hipStreamSynchronize(s_);
-        if (!finished_) h_->pts_k = -1; // the points on the device are not known
+        if (count_ > 0 && !finished_) h_->pts_k = -1; // the points on the device are not known
         for (Slot &q : slot_) {
             pinned_put(q.mem, q.cap);
             if (q.sent) event_put(q.sent);
@@ -726,6 +733,9 @@ public:
         if (!q.mem) e = hipStreamSynchronize(ws); // h->pts is still being read
         else if (count_ >= 2) e = hipEventSynchronize(q.sent);
         if (e != hipSuccess) return e;
+        // (the slot's draw is on ws after the one before it)
+        ended_ = q.mem ? std::max(0, count_ - 2) : count_;
+        if (count_++ == 0) first_drawn_ = k;
         make_points(h_, k, h_->pts);
         if (q.mem) std::memcpy(q.mem, h_->pts.data(), bytes);
         if (side_ && in_use_[t]) e = hipStreamWaitEvent(side_, used_[t], 0);
@@ -734,10 +744,10 @@ public:
                                hipMemcpyHostToDevice, ws);
         if (e == hipSuccess) e = hipEventRecord(q.sent, ws);
         if (e == hipSuccess)
-            e = pinv_->enqueue(ws, status() + count_, set_[t].pts, set_[t].W, side_ && long_path_);
+            e = pinv_->enqueue(ws, status() + count_ - 1, set_[t].pts, set_[t].W,
+                               side_ && long_path_);
         if (e == hipSuccess && side_) e = hipEventRecord(ready_[t], side_);
         if (e != hipSuccess) return e;
-        ++count_;
         h_->pts_k = drawn_ = k;
         return hipSuccess;
     }
@@ -778,11 +788,20 @@ public:
         return e;
     }
 
-    bool full_rank()
+    bool failed() { return deficient(ended_) < ended_; }
+    bool full_rank() { return deficient(count_) == count_; }
+    void restore()
     {
-        for (int i = 0; i < count_; ++i)
-            if (status()[i] != 0) return false;
-        return true;
+        h_->pts_k = -1;
+        if (side_ && hipStreamSynchronize(side_) != hipSuccess) return;
+        const int i = deficient(count_), k = i == 0 ? from_ : first_drawn_ + i - 1;
+        if (k < 0) return;
+        make_points(h_, k, h_->pts);
+        hipError_t e = hipMemcpyAsync(h_->d_pts, h_->pts.data(), sizeof(double) * h_->pts.size(),
+                                      hipMemcpyHostToDevice, s_);
+        if (e == hipSuccess) e = pinv_->enqueue(s_, status(), h_->d_pts, h_->d_W, false);
+        const hipError_t se = hipStreamSynchronize(s_);
+        if (e == hipSuccess && se == hipSuccess && status()[0] == 0) h_->pts_k = k;
     }
 
 private:
@@ -825,6 +844,13 @@ private:
     // the set of iteration k: the problem's own first
     int target(int k) const { return side_ ? (k - first_) & 1 : 0; }
     int *status() { return pinned_status_ ? pinned_status_ : status_.data(); }
+    // the first of `count` draws whose rank test failed, or count
+    int deficient(int count)
+    {
+        int i = 0;
+        while (i < count && status()[i] == 0) ++i;
+        return i;
+    }
     struct Slot {
         void *mem = nullptr;
         size_t cap = 0;
@@ -841,7 +867,10 @@ private:
     int *pinned_status_ = nullptr;
     std::vector<int> status_;
     size_t status_cap_ = 0;
-    int count_ = 0, first_ = 0, drawn_ = -1, last_ = 0;
+    // draws begun, those of them known to have ended, the first one's
+    // iteration; the iteration whose points the solve began with
+    int count_ = 0, ended_ = 0, first_drawn_ = 0, from_;
+    int first_ = 0, drawn_ = -1, last_ = 0;
 };
 } // namespace
 
@@ -1466,13 +1495,13 @@ bsde_status bsde_solve(bsde_problem h, void *hip_stream)
         auto draw = [&](int kk) {
             const hipError_t re = redraw.draw(kk, ev[0]);
             if (re == hipSuccess) return BSDE_OK;
-            h->pts_k = -1; // the points on the device are not known
             return fail(re == hipErrorOutOfMemory ? BSDE_ENOMEM : BSDE_EDEVICE,
                         std::string("redrawn points: ") + hipGetErrorString(re));
         };
         RedrawWork::Set set{h->d_pts, h->d_W};
         if (h->redraw) {
             if (!redraw.drawn(k) && h->pts_k != k && (st = draw(k)) != BSDE_OK) return st;
+            if (redraw.failed()) break;
             HIP_TRY(redraw.begin(k, set));
         }
         PathParams prm = h->base;
@@ -1520,6 +1549,10 @@ bsde_status bsde_solve(bsde_problem h, void *hip_stream)
     HIP_TRY(hipMemcpyAsync(alpha.get() ? alpha.get() : (void *)h->alpha_hist.data(), h->d_alpha,
                            alpha_bytes, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    if (!redraw.full_rank()) {
+        redraw.restore();
+        return fail(BSDE_ERANK, kRankMessage);
+    }
     double t_path = 0, t_fin = 0, t_proj = 0, t_chan = 0;
     for (int it = 0; it < iters && per; ++it) {
         hipEvent_t *e = &ev[2 + (size_t)per * it];
@@ -1538,10 +1571,6 @@ bsde_status bsde_solve(bsde_problem h, void *hip_stream)
     }
     float tot;
     hipEventElapsedTime(&tot, ev[0], ev[1]);
-    if (!redraw.full_rank()) {
-        h->pts_k = -1;
-        return fail(BSDE_ERANK, kRankMessage);
-    }
     if (alpha.get()) std::memcpy(h->alpha_hist.data(), alpha.get(), alpha_bytes);
     if (iters > 0) {
         h->timings[0] = t_path / iters;
@@ -2224,6 +2253,17 @@ bsde_status bsde_fit_values(bsde_problem h, const double *y, int k_done)
     if (!h || !y) return fail(BSDE_EINVAL, "null argument");
     if (k_done < 0 || k_done > h->K_it) return fail(BSDE_EINVAL, "bad k_done");
     if (h->kop) return fail(BSDE_EUNSUPPORTED, "the kernel operator fits no basis");
+    if (h->redraw && h->pts_k < 0) {
+        // a solve ended in a device error, and W may not be that of the points
+        hipStream_t s = nullptr;
+        HIP_TRY(setup_stream_get(&s));
+        hipError_t e = hipMemcpyAsync(h->d_pts, h->pts.data(), sizeof(double) * h->pts.size(),
+                                      hipMemcpyHostToDevice, s);
+        const bsde_status st = device_pseudo_inverse(h, s);
+        setup_stream_put(s);
+        HIP_TRY(e);
+        if (st != BSDE_OK) return st;
+    }
     // alpha = R^{-1} Q' y = W y on the device (0.10 ms with its copies
     // at n = 10933, p = 56; W copied back and multiplied on the host: 0.60 ms)
     const int segs = project_segments(h->n);
