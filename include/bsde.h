@@ -90,8 +90,8 @@ typedef struct {
 /* The n points (t_i, x_i) of Algorithm "algodetail" and the basis of the
  * least-squares extrapolating operator (Section 4.2, eqs. lspb and
  * hyper_set).  Points are fixed for all iterations.  Point i is
- * a * n_spatial + b for time node a (t_a = a T / (n_t - 1)) and spatial
- * point b.  The domain is D_j = log S0_j +- width * level_j * sqrt(T);
+ * a * n_spatial + b for time node a (t_a = a T / (n_t - 1), the last T itself)
+ * and spatial point b.  The domain is D_j = log S0_j +- width * level_j * sqrt(T);
  * polynomials are Chebyshev in the variables mapped to [-1, 1]^{d+1}. */
 typedef enum {
     BSDE_GRID_TENSOR = 0, /* n_x equispaced nodes per asset (endpoints

@@ -214,7 +214,8 @@ int oracle_points_k(const oracle_problem *pb, uint32_t k, double *pts)
     double lo[ORACLE_DMAX], hi[ORACLE_DMAX];
     oracle_domain(pb, lo, hi);
     for (int a = 0; a < pb->n_t; ++a) {
-        double t = (double)a * pb->T / (double)(pb->n_t - 1);
+        /* the last node is T itself, which the product can miss by its rounding */
+        double t = a == pb->n_t - 1 ? pb->T : (double)a * pb->T / (double)(pb->n_t - 1);
         for (long b = 0; b < ns; ++b) {
             double *row = pts + (size_t)(a * ns + b) * (d + 1);
             row[0] = t;

@@ -478,7 +478,8 @@ static void make_points(const bsde_problem_s *h, int k, std::vector<double> &pts
         }
     }
     for (int a = 0; a < h->n_t; ++a) {
-        const double t = a * h->base.T / (h->n_t - 1);
+        // (the last is T itself, which the product can miss by its rounding)
+        const double t = a == h->n_t - 1 ? h->base.T : a * h->base.T / (h->n_t - 1);
         double *rows = &pts[(size_t)a * ns * dp];
         if (a) std::memcpy(rows, pts.data(), sizeof(double) * (size_t)ns * dp);
         for (long s = 0; s < ns; ++s) rows[(size_t)s * dp] = t;
