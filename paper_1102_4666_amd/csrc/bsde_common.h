@@ -487,8 +487,9 @@ struct PathParams {
 
 // Extrapolating operators: least squares on the polynomial basis, or the
 // kernel operator of Section 3.2 (path kernels with OP = kOpKernel read a
-// table of rows {z_0, .., z_d, y} of kKernelRow entries instead of Gamma)
-enum { kOpBasis = 0, kOpKernel = 1 };
+// table of rows {z_0, .., z_d, y} of kKernelRow entries instead of Gamma, those
+// with OP = kOpProduct the product table below)
+enum { kOpBasis = 0, kOpKernel = 1, kOpProduct = 2 };
 constexpr int kKernelRow = 4;
 // weights beyond this exponent are constant (the clamp of the kernel)
 constexpr double kKernelClamp = 60.0;

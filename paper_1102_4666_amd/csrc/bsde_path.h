@@ -853,7 +853,7 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
         // Phi(X_T) - u^k(T, X_T)
         Real phi_tau = payoff<D>(prm.payoff, K, Xt);
         Real u = Real(0), gen = Real(0), uT = Real(0), terminal;
-        if constexpr (OP == kOpKernel) {
+        if constexpr (OP != kOpBasis) {
             // u^k = h[y] of the kernel operator (Section 3.2) in its
             // normalised form h = S1 / S0, S0 = sum_i w_i, S1 = sum_i y_i w_i,
             // w_i = exp(-min(|z - z_i|^2 / (2 b^2), clamp)) in the mapped
@@ -905,7 +905,7 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
             Real G0[D], G1[D]; // sum w dz_j and sum y w dz_j (unclamped weights)
 #pragma unroll
             for (int j = 0; j < D; ++j) G0[j] = G1[j] = Real(0);
-            if (prm.kop_nt > 0) {
+            if constexpr (OP == kOpProduct) {
                 // Product points: e^{-e} of a pair is the product of its
                 // time node's and its spatial point's factors, so a pair
                 // costs a product, a maximum (the clamp: max(e^{-e}, e^{-clamp})
@@ -915,7 +915,7 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
                 // factors wait in LDS; the sums over a spatial point's times
                 // of the unclamped weights and their first moments in dz_0
                 // give the moments in dz_j.
-                __shared__ Real kop_w[OP == kOpKernel ? kKopTimes : 1][kBlock];
+                __shared__ Real kop_w[kKopTimes][kBlock];
                 const int nt = prm.kop_nt, ns = prm.n / nt, stride = kop_row(D, nt);
                 auto factor = [&](Real e) {
                     if constexpr (kF32) return __builtin_amdgcn_exp2f(-e);
@@ -1332,7 +1332,12 @@ int copy_index_table(int8_t *nu, int cap)
 // Dupire) sets listed by SETS(X) as X(E, Q, PREC, DUP), with q = Q / 10 and
 // PREC a PrecisionSet.
 // Path kernels of the kernel operator (Section 3.2) for d = D: FP32 and
-// FP64 paths, constant and bump volatility; table = rows {z, y}
+// FP64 paths, constant and bump volatility; table = rows {z, y} or, when the
+// problem has one, the product table.  A kernel for each: the product form's
+// factors in LDS and its registers would cost the plain rows waves they have no
+// use for (FP64 d = 1 four a SIMD to two, FP32 eight to six;
+// 3000 uniform points, M = 300, N = 20, bump: 7.91 ms in one kernel for both,
+// 7.21 apart in FP64 at d = 2, 6.59 and 6.27 at d = 1, 2.22 and 2.13 in FP32)
 #define BSDE_DEFINE_KERNEL_OP(D)                                               \
     hipError_t launch_kernel_path_d##D(bool fp32, int blocks, hipStream_t s,   \
                                        const PathParams &prm,                  \
@@ -1343,10 +1348,15 @@ int copy_index_table(int8_t *nu, int cap)
         return dispatch_variant<D, 1, kPrecBoth, false>(                            \
             fp32, prm.vol_kind, [&](auto rt, auto vt) -> hipError_t {          \
                 using R = typename decltype(rt)::type;                         \
-                hipExtLaunchKernelGGL(                                         \
-                    (path_kernel<D, 1, R, decltype(vt)::value, 10, kOpKernel>), \
-                    dim3(blocks), dim3(kBlock), 0, s, ev0, ev1, 0u, prm, pts,  \
-                    (const R *)table, partial);                                \
+                constexpr int V = decltype(vt)::value;                         \
+                if (prm.kop_nt > 0)                                            \
+                    hipExtLaunchKernelGGL((path_kernel<D, 1, R, V, 10, kOpProduct>), \
+                                          dim3(blocks), dim3(kBlock), 0, s, ev0, ev1, \
+                                          0u, prm, pts, (const R *)table, partial); \
+                else                                                           \
+                    hipExtLaunchKernelGGL((path_kernel<D, 1, R, V, 10, kOpKernel>), \
+                                          dim3(blocks), dim3(kBlock), 0, s, ev0, ev1, \
+                                          0u, prm, pts, (const R *)table, partial); \
                 return hipGetLastError();                                      \
             });                                                                \
     }
