@@ -993,6 +993,19 @@ const char *bsde_last_error(void) { return g_last_error.c_str(); }
 static bsde_status prepare_tiling(bsde_problem h, int &groups, int &ppl,
                                   bool allow_alloc = true);
 
+// Points of a grid and how many of them are spatial ones; 0 when its numbers
+// are out of range or the points more than the 2^26 a problem may have
+static int grid_points(int d, const bsde_grid *grid, int *spatial)
+{
+    const long most = 1L << 26, n_t = grid->kind == BSDE_GRID_UNIFORM ? 1 : grid->n_t;
+    if (grid->n_x < 1 || n_t < 1) return 0;
+    long ns = grid->n_x;
+    for (int j = 1; j < d && grid->kind == BSDE_GRID_TENSOR && ns <= most; ++j) ns *= grid->n_x;
+    if (ns > most || ns * n_t > most) return 0;
+    *spatial = (int)ns;
+    return (int)(ns * n_t);
+}
+
 extern "C" {
 
 bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
@@ -1121,27 +1134,15 @@ bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
     }
     h->C = num_channels(d);
 
-    // grid points (time-major)
-    long ns = 1;
-    if (grid->kind == BSDE_GRID_TENSOR) {
-        for (int j = 0; j < d; ++j) {
-            ns *= grid->n_x;
-            if (ns > (1L << 26)) {
-                delete h;
-                return fail(BSDE_EINVAL, "tensor grid too large");
-            }
-        }
-    } else {
-        ns = grid->n_x;
-    }
-    // uniform points: n_x of them, no time nodes
+    // grid points (time-major); uniform points: n_x of them, no time nodes
+    int ns = 0;
     const int n_t = grid->kind == BSDE_GRID_UNIFORM ? 1 : grid->n_t;
-    if ((long)ns * n_t > (1L << 26)) {
+    h->n = grid_points(d, grid, &ns);
+    if (h->n == 0) {
         delete h;
         return fail(BSDE_EINVAL, "too many points");
     }
-    h->n_spatial = (int)ns;
-    h->n = (int)(ns * n_t);
+    h->n_spatial = ns;
     h->grid_kind = grid->kind;
     h->n_t = n_t;
     h->n_x = grid->n_x;
@@ -1911,17 +1912,15 @@ bsde_status bsde::fetch_coefficients(bsde_problem h)
     return BSDE_OK;
 }
 
-size_t bsde::problem_device_bytes(int d, const bsde_grid *grid, int M, int K_it)
+size_t bsde::problem_device_bytes(int d, const bsde_grid *grid, int M, int N, int K_it)
 {
-    if (d < 1 || d > kMaxD || !grid) return 0;
+    // (what bsde_create_problem refuses takes no memory)
+    if (d < 1 || d > kMaxD || !grid || M < 1 || N < 1 || K_it < 1) return 0;
     const int p = index_table(d, grid->eta, kernel_q10(d, grid->eta, grid->q), nullptr, 0);
     if (p == 0) return 0;
-    size_t ns = 1;
-    if (grid->kind == BSDE_GRID_TENSOR)
-        for (int j = 0; j < d; ++j) ns *= (size_t)grid->n_x;
-    else
-        ns = (size_t)grid->n_x;
-    const size_t n = ns * (size_t)(grid->kind == BSDE_GRID_UNIFORM ? 1 : grid->n_t);
+    int ns = 0;
+    const size_t n = (size_t)grid_points(d, grid, &ns);
+    if (n == 0) return 0;
     const size_t C = (size_t)num_channels(d);
     bsde_problem_s tmp;
     tmp.n = (int)n;

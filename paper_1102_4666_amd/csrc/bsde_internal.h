@@ -75,6 +75,7 @@ bsde_status run_batch(bsde_problem *probs, int count, hipStream_t s, int steps,
                       int cu_reserve = 0);
 // copies the latest coefficients of a finished problem back to the host
 bsde_status fetch_coefficients(bsde_problem h);
-// device bytes a problem with these parameters allocates (pool size classes)
-size_t problem_device_bytes(int d, const bsde_grid *grid, int M, int K_it);
+// device bytes a problem with these parameters allocates (pool size classes);
+// 0 for parameters that are refused
+size_t problem_device_bytes(int d, const bsde_grid *grid, int M, int N, int K_it);
 } // namespace bsde

@@ -317,7 +317,7 @@ bsde_status bsde_server_submit(bsde_server S, const bsde_request *req,
     q->penalty = req->penalty;
     q->qt = req->query_t;
     q->seed = req->seed;
-    q->bytes = problem_device_bytes(d, &req->grid, req->M, req->n_picard);
+    q->bytes = problem_device_bytes(d, &req->grid, req->M, req->N, req->n_picard);
     size_t ns = 1;
     if (req->grid.kind == BSDE_GRID_TENSOR)
         for (int j = 0; j < d; ++j) ns *= (size_t)std::max(1, req->grid.n_x);
