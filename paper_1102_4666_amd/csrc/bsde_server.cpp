@@ -318,6 +318,16 @@ bsde_status bsde_server_submit(bsde_server S, const bsde_request *req,
     q->qt = req->query_t;
     q->seed = req->seed;
     q->bytes = problem_device_bytes(d, &req->grid, req->M, req->N, req->n_picard);
+    // no memory: bsde_create_problem refuses it, before it reaches the device,
+    // and says why
+    bsde_status refused = BSDE_OK;
+    if (q->bytes == 0) {
+        bsde_problem h = nullptr;
+        refused = bsde_create_problem(d, &q->sigma, q->r, &q->payoff, &q->grid, q->M, q->N,
+                                      q->K_it, q->penalty, q->seed, q->precision, &h);
+        bsde_destroy(h);
+        if (refused == BSDE_OK) refused = BSDE_EINVAL;
+    }
     size_t ns = 1;
     if (req->grid.kind == BSDE_GRID_TENSOR)
         for (int j = 0; j < d; ++j) ns *= (size_t)std::max(1, req->grid.n_x);
@@ -336,9 +346,9 @@ bsde_status bsde_server_submit(bsde_server S, const bsde_request *req,
         S->t_first = q->t_submit;
     }
     S->tickets[q->ticket] = q;
-    if (q->bytes == 0) { // unsupported (d, eta): fail the ticket at once
+    if (refused != BSDE_OK) { // fail the ticket at once
         q->t_start = q->t_submit;
-        complete(S, q, BSDE_EUNSUPPORTED);
+        complete(S, q, refused);
         S->cv_done.notify_all();
     } else {
         S->pending.push_back(q);
