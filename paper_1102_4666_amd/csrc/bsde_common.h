@@ -3,6 +3,8 @@
 // sets of the polynomial basis and the per-launch parameter block.
 #pragma once
 
+#include "bsde_tiling.h"
+
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -28,7 +30,6 @@ __host__ __device__ __forceinline__ void static_for(F &&f)
 }
 
 constexpr int kMaxD = 10;
-constexpr int kBlock = 256; // lanes per workgroup of the path kernel
 // largest padded basis whose set-up factorisations run in one workgroup with
 // the matrices in LDS, and the most 16-column tiles of any basis (448
 // functions; the largest set built has 386)

@@ -946,26 +946,6 @@ TuneKey tune_key(const bsde_problem_s *h)
 }
 } // namespace
 
-static void auto_tiling(const bsde_problem_s *h, int &groups, int &ppl)
-{
-    // Up to 16 384 tiles of two blocks of paths or more, and single blocks up
-    // to 2048 tiles.  1024 workgroups run at a time in the FP32 d = 1 kernel,
-    // and rounds of long tiles end with idle units: n = 2048, M = 4000 takes
-    // 0.280 ms in 2048 tiles, 0.250 in 16 384, 0.262 in 32 768 of one block
-    // (d = 10, q = 0.6, n = 1000, M = 30 000: 3.00, 2.80, 2.92 ms).  A tile of
-    // one block pays for its start and reduction as much as a longer one:
-    // alone that is the same (n = 2048, M = 1000: 0.077 ms in tiles of one and
-    // of two), but a batch, which has tiles enough, loses by it (eight
-    // problems, M = 550: 8.8 ms in single blocks, 7.0 in tiles of three).
-    // From n = 8193 on one group is as fast as several (d = 2, n = 16 384,
-    // M = 2000: 1.895 ms against 1.907 in two).
-    const int blocks = (h->M + kBlock - 1) / kBlock;
-    const int fill = (2048 + h->n - 1) / h->n, most = std::min(16384 / h->n, blocks / 2);
-    const int want = std::max(1, std::min(blocks, std::max(fill, most)));
-    ppl = (blocks + want - 1) / want;
-    groups = (blocks + ppl - 1) / ppl;
-}
-
 // ---------------------------------------------------------------------------
 // C ABI
 // ---------------------------------------------------------------------------
@@ -1429,7 +1409,7 @@ static bsde_status prepare_tiling(bsde_problem h, int &groups, int &ppl,
 {
     groups = h->groups;
     ppl = h->ppl;
-    if (groups == 0) auto_tiling(h, groups, ppl);
+    if (groups == 0) auto_tiling(h->n, h->M, h->N, h->d, groups, ppl);
     const size_t need = (size_t)h->n * groups * 2;
     if (need > h->partial_cap) {
         if (!allow_alloc)
@@ -1922,11 +1902,8 @@ size_t bsde::problem_device_bytes(int d, const bsde_grid *grid, int M, int N, in
     const size_t n = (size_t)grid_points(d, grid, &ns);
     if (n == 0) return 0;
     const size_t C = (size_t)num_channels(d);
-    bsde_problem_s tmp;
-    tmp.n = (int)n;
-    tmp.M = M;
     int groups, ppl;
-    auto_tiling(&tmp, groups, ppl);
+    auto_tiling((int)n, M, N, d, groups, ppl);
     // the block of points, the channel update's sparse rows, coefficients
     // and tables (one allocation, 256-byte aligned parts), then the separate
     // buffers; at most p C table entries, each row of the update at most 16
