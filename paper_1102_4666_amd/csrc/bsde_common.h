@@ -391,32 +391,6 @@ struct ChannelRows {
 // each j: g_j, for each k >= j: h_jk, for each l >= k: c_jkl (coefficients of
 // the monomials).  c_4v, c_5v of every variate, when there are any, at off_q.
 // ---------------------------------------------------------------------------
-// 0: the set nu(l, v), l < p, v < dp does not have the form (or d < 3, where
-// the channels are as cheap); 1: a cubic; 2: with single-variate terms of
-// degree 4 or 5
-template <typename Nu>
-__host__ __device__ constexpr int cubic_kind(const Nu &nu, int p, int dp)
-{
-    if (dp < 4) return 0;
-    int top = 0;
-    for (int l = 0; l < p; ++l) {
-        int deg = 0, parts = 0;
-        for (int v = 0; v < dp; ++v) {
-            deg += nu(l, v);
-            parts += nu(l, v) > 0;
-        }
-        if (deg > 3 && (parts > 1 || deg > 5)) return 0;
-        if (deg > top) top = deg;
-    }
-    // (at degree 2 the Hessian is constant and the channels cost less)
-    return top < 3 ? 0 : top == 3 ? 1 : 2;
-}
-template <int DP, int ETA, int Q>
-constexpr int cubic_kind_of()
-{
-    using BS = Basis<DP, ETA, Q>;
-    return cubic_kind([](int l, int v) { return (int)BS::tab.nu[l][v]; }, BS::P, DP);
-}
 struct CubicLayout {
     int pairs, rows, ka;       // Hessian pairs, rows at tau, coefficients a row
     int pairs_t, rows_t, kt;   // the same for u(T, x)
@@ -434,6 +408,47 @@ struct CubicLayout {
     // groups of four rows
     __host__ __device__ static constexpr int groups(int r) { return (r + 3) / 4; }
 };
+
+// 0: the set nu(l, v), l < p, v < dp does not have the form, or the channels
+// cost less (d < 3, and see below); 1: a cubic; 2: with single-variate terms of
+// degree 4 or 5
+template <typename Nu>
+__host__ __device__ constexpr int cubic_kind(const Nu &nu, int p, int dp)
+{
+    if (dp < 4) return 0;
+    int top = 0, live = p; // live: entries of the channel table (a multi-index
+                           // counts for each derivative that it has)
+    for (int l = 0; l < p; ++l) {
+        int deg = 0, parts = 0, spatial = 0;
+        for (int v = 0; v < dp; ++v) {
+            deg += nu(l, v);
+            parts += nu(l, v) > 0;
+            spatial += v > 0 && nu(l, v) > 0;
+            live += v > 0 && nu(l, v) > 1;
+        }
+        live += parts + spatial * (spatial - 1) / 2;
+        if (deg > 3 && (parts > 1 || deg > 5)) return 0;
+        if (deg > top) top = deg;
+    }
+    // (at degree 2 the Hessian is constant and the channels cost less)
+    if (top < 3) return 0;
+    // A matrix product of the form takes as long as a vector product of a
+    // channel: the sparse sets, with fewer live entries than the form has
+    // products, are faster in the channels (d = 10, 394 products; a batch of six,
+    // n = 3072, M = 700, N = 10, in the form and in channels: eta = 4, q = 0.6, 329
+    // entries, 2.73 and 2.28 ms; eta = 5, q = 0.5, 361 entries, 2.72 and 2.32;
+    // eta = 5, q = 0.6, 881 entries, 2.75 and 3.33)
+    const CubicLayout lay(dp - 1, true, 1);
+    if (live <= CubicLayout::groups(lay.rows) * lay.ka + CubicLayout::groups(lay.rows_t) * lay.kt)
+        return 0;
+    return top == 3 ? 1 : 2;
+}
+template <int DP, int ETA, int Q>
+constexpr int cubic_kind_of()
+{
+    using BS = Basis<DP, ETA, Q>;
+    return cubic_kind([](int l, int v) { return (int)BS::tab.nu[l][v]; }, BS::P, DP);
+}
 
 // ---------------------------------------------------------------------------
 // Per-launch parameters of the path kernel (passed by value).

@@ -1103,8 +1103,10 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
                 // degree zero)
                 static_for<NP>([&](auto lc) {
                     constexpr int l = decltype(lc)::value;
-                    if constexpr (BS::tab.nu[l][0] == 0)
-                        uT = fma(basis(lc, TzT), pk[CR::tab.goff[NP] + terminal_index<BS>(l)], uT);
+                    if constexpr (BS::tab.nu[l][0] == 0) {
+                        constexpr int e = CR::tab.goff[NP] + terminal_index<BS>(l);
+                        uT = fma(basis(lc, TzT), pk[e], uT);
+                    }
                 });
                 terminal = payoff<D>(prm.payoff, K, X) - uT;
                 // second derivatives first, one channel at a time, each
