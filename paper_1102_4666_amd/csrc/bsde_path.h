@@ -618,11 +618,16 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
     // group makes no block beyond its last step.  Not at d = 10, two steps a
     // group: at the FP64 kernels' two waves per SIMD the blocks made together
     // hide each other's latencies (8192 points, M = 500, N = 50: 4.49 ms
-    // against 4.95), and the FP32 kernels would spill more; the FP64 ones
-    // outside the cubic form (degree 2) would spill more made together.
-    constexpr bool kLateNormals =
-        NB > 1 && (D < 10 || (sizeof(Real) == 8 && !kCubic));
+    // against 4.95; degree 2, constant volatility, 3072 points, M = 1000, N = 50:
+    // 2.05 against 2.20), and the FP32 kernels would spill more.
+    constexpr bool kLateNormals = NB > 1 && D < 10;
     constexpr bool kXor3 = sizeof(Real) == 4 || D >= 2; // Philox XOR form
+    // FP64 at d = 10: the constant volatilities pass through an empty asm
+    // statement on each path, so that what follows from them alone (55 entries of
+    // the covariance) is formed there and not kept across the path loop, in
+    // scratch memory for the most part (degree 2, 3072 points, M = 1000: N = 5
+    // 0.626 -> 0.457 ms, N = 50 2.19 -> 2.05)
+    constexpr bool kOpaqueVol = VOL == kVolConst && sizeof(Real) == 8 && D >= 10;
     // FP32 round keys in vector registers (16 of them): at d = 1, and at
     // d = 2 from eta = 5 on, where the kernel's own registers already hold
     // it to four waves per SIMD and the keys still fit (below, they would
@@ -844,6 +849,7 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
             if (j + 1 < D) Sb = j == 0 ? ac.Lcol[0] * Gb[0] : fma(ac.Lcol[j], Gb[j], Sb);
             sgs[j] = local_vol<VOL>(ac.level[j], ac.level_a[j], lc, ac.spot[j], vts,
                                     Xs[j]);
+            if constexpr (kOpaqueVol) asm volatile("" : "+v"(sgs[j]));
             bst[j] = fma(Real(-0.5) * sgs[j], sgs[j], ac.drift[j]);
             Xt[j] = Xs[j] + bst[j] * theta * h +
                     sgs[j] * fma(theta, LGs[j], lgb);
