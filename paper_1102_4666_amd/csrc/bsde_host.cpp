@@ -1259,8 +1259,8 @@ bsde_status bsde_create_problem(int d, const bsde_sigma *sigma, double r,
                  o_ktab = o_col + al256(b_col), n_block = o_ktab + al256(b_ktab);
     bool ok = dalloc(&h->d_block, n_block) &&
               (kop || dalloc((void **)&h->d_W, sizeof(double) * (size_t)h->p * h->n)) &&
-              dalloc((void **)&h->d_beta,
-                     sizeof(double) * h->p * (size_t)project_segments(h->n)) &&
+              (kop || dalloc((void **)&h->d_beta,
+                             sizeof(double) * h->p * (size_t)project_segments(h->n))) &&
               dalloc((void **)&h->d_c, sizeof(double) * (size_t)h->K_it * h->n) &&
               dalloc((void **)&h->d_var, sizeof(double) * (size_t)h->K_it * h->n);
     if (!ok) {
@@ -1906,9 +1906,10 @@ size_t bsde::problem_device_bytes(int d, const bsde_grid *grid, int M, int N, in
     auto_tiling((int)n, M, N, d, groups, ppl);
     // the block of points, the channel update's sparse rows, coefficients
     // and tables (one allocation, 256-byte aligned parts), then the separate
-    // buffers; at most p C table entries, each row of the update at most 16
-    // non-zeros (a row of a mixed second derivative has one per pair of odd
-    // degree steps k1 + k2 <= eta: 10 at eta = 8, the most of any set built)
+    // buffers; at most p C table entries and 16 p C non-zeros of the update in
+    // all (a row of the channels has at most 10, of a mixed second derivative at
+    // eta = 8: one per pair of odd degree steps k1 + k2 <= eta; one of the cubic
+    // form up to 36, and the form's rows are less than a fifth of p C)
     auto al256 = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t entries = table_entries(p, (int)C), nonzeros = 16 * entries;
     const size_t block = al256(n * (d + 1) * 8) + al256(nonzeros * 8) +
@@ -1921,11 +1922,14 @@ size_t bsde::problem_device_bytes(int d, const bsde_grid *grid, int M, int N, in
                             n * groups * 16};
     size_t total = 0;
     for (size_t b : sizes) total += size_class(b == 0 ? 8 : b);
-    // transient set-up buffers: two point matrices and the Gram partials
+    // transient set-up buffers (PseudoInverse): two point matrices, the Gram
+    // partials, the p x p matrices and the small inputs
     int ld, rpc, chunks;
-    setup_shape((int)n, pad16(p), ld, rpc, chunks);
-    total += 2 * size_class((size_t)ld * pad16(p) * 8) +
-             size_class((size_t)chunks * pad16(p) * pad16(p) * 8);
+    const size_t pap = (size_t)pad16(p);
+    setup_shape((int)n, (int)pap, ld, rpc, chunks);
+    total += 2 * size_class((size_t)ld * pap * 8) + size_class((size_t)chunks * pap * pap * 8) +
+             size_class((3 * pap * pap + factor_workspace((int)pap)) * 8) +
+             size_class((size_t)p * (d + 1 + sizeof(int)) + 1024);
     return total;
 }
 
