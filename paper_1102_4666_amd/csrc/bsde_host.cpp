@@ -2208,13 +2208,16 @@ bsde_status bsde_get_coefficients(bsde_problem h, int k, double *alpha,
     return BSDE_OK;
 }
 
-static bsde_status store_alpha(bsde_problem h, const double *alpha, int k_done)
+// on_device: they are there already
+static bsde_status store_alpha(bsde_problem h, const double *alpha, int k_done,
+                               bool on_device = false)
 {
     for (int l = 0; l < h->p; ++l)
         h->alpha_hist[(size_t)k_done * h->p + l] = h->active[l] ? alpha[l] : 0.0;
-    HIP_TRY(hipMemcpy(h->d_alpha + (size_t)k_done * h->p,
-                      &h->alpha_hist[(size_t)k_done * h->p],
-                      sizeof(double) * h->p, hipMemcpyHostToDevice));
+    if (!on_device)
+        HIP_TRY(hipMemcpy(h->d_alpha + (size_t)k_done * h->p,
+                          &h->alpha_hist[(size_t)k_done * h->p],
+                          sizeof(double) * h->p, hipMemcpyHostToDevice));
     h->k_done = k_done;
     h->have_alpha = true;
     return BSDE_OK;
@@ -2245,32 +2248,49 @@ bsde_status bsde_fit_values(bsde_problem h, const double *y, int k_done)
         HIP_TRY(e);
         if (st != BSDE_OK) return st;
     }
-    // alpha = R^{-1} Q' y = W y on the device (0.10 ms with its copies
-    // at n = 10933, p = 56; W copied back and multiplied on the host: 0.60 ms)
+    // alpha = R^{-1} Q' y = W y on the device, without memory of its own: y goes to
+    // the paths' moments, which every iteration writes anew (n = 10 933, p = 56:
+    // 41 us; W copied back and multiplied on the host: 590).  Up to 16 384 entries
+    // of W the kernel takes y from pinned memory and leaves its sums there, with
+    // one wait and no copy (n = 9, p = 6: 19 us, 23 on the host; n = 512, p = 15: 22
+    // and 35, and 41 with the copies).
     const int segs = project_segments(h->n);
     const size_t y_bytes = sizeof(double) * (size_t)h->n;
-    double *dy = nullptr;
-    hipStream_t us = nullptr;
     std::vector<double> a((size_t)segs * h->p, 0.0);
-    hipError_t e = pool_alloc((void **)&dy, y_bytes);
-    if (e == hipSuccess) e = setup_stream_get(&us);
-    if (e == hipSuccess) e = hipMemcpyAsync(dy, y, y_bytes, hipMemcpyHostToDevice, us);
-    if (e == hipSuccess) e = launch_project(h->d_W, dy, h->n, h->p, h->d_beta, us);
+    const size_t a_bytes = sizeof(double) * a.size();
+    if (h->partial_cap < (size_t)h->n) {
+        int groups, ppl;
+        const bsde_status st = prepare_tiling(h, groups, ppl);
+        if (st != BSDE_OK) return st;
+    }
+    PinnedBuffer pin(y_bytes + a_bytes);
+    double *py = (double *)pin.get(), *pa = py ? py + h->n : nullptr;
+    const bool direct = py && segs == 1 && (size_t)h->n * h->p <= 16384;
+    // (with every function active the sums are the coefficients)
+    const bool in_place = direct && h->act.size() == (size_t)h->p;
+    if (py) std::memcpy(py, y, y_bytes);
+    hipStream_t us = nullptr;
+    hipError_t e = setup_stream_get(&us);
+    if (e == hipSuccess && !direct)
+        e = hipMemcpyAsync(h->d_partial, py ? py : y, y_bytes, hipMemcpyHostToDevice, us);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(a.data(), h->d_beta, sizeof(double) * a.size(), hipMemcpyDeviceToHost,
+        e = launch_project(h->d_W, direct ? py : h->d_partial, h->n, h->p, direct ? pa : h->d_beta,
                            us);
+    if (e == hipSuccess && in_place)
+        e = launch_project(h->d_W, py, h->n, h->p, h->d_alpha + (size_t)k_done * h->p, us);
+    if (e == hipSuccess && !direct)
+        e = hipMemcpyAsync(pa ? pa : a.data(), h->d_beta, a_bytes, hipMemcpyDeviceToHost, us);
     if (us) {
         const hipError_t se = hipStreamSynchronize(us);
         if (e == hipSuccess) e = se;
         setup_stream_put(us);
     }
-    pool_free(dy);
     if (e != hipSuccess)
-        return fail(e == hipErrorOutOfMemory ? BSDE_ENOMEM : BSDE_EDEVICE,
-                    std::string("fit: ") + hipGetErrorString(e));
+        return fail(BSDE_EDEVICE, std::string("fit: ") + hipGetErrorString(e));
+    if (pa) std::memcpy(a.data(), pa, a_bytes);
     for (int q = 1; q < segs; ++q)
         for (int l = 0; l < h->p; ++l) a[l] += a[(size_t)q * h->p + l];
-    return store_alpha(h, a.data(), k_done);
+    return store_alpha(h, a.data(), k_done, in_place);
 }
 
 bsde_status bsde_get_corrections(bsde_problem h, int k, double *c, double *var)
