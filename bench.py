@@ -219,6 +219,7 @@ COUNTERS = [
 FETCH_FACTOR, WRITE_FACTOR = 2.0, 1.0
 KERNEL_SOURCES = ("paper_1102_4666_amd/csrc/bsde_path.h",
                   "paper_1102_4666_amd/csrc/bsde_common.h",
+                  "paper_1102_4666_amd/csrc/bsde_tiling.h",
                   "paper_1102_4666_amd/csrc/bsde_f64_math.h",
                   "paper_1102_4666_amd/csrc/bsde_inst_d5.hip")
 

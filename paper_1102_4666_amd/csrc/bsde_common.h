@@ -437,7 +437,9 @@ __host__ __device__ constexpr int cubic_kind(const Nu &nu, int p, int dp)
     // products, are faster in the channels (d = 10, 394 products; a batch of six,
     // n = 3072, M = 700, N = 10, in the form and in channels: eta = 4, q = 0.6, 329
     // entries, 2.73 and 2.28 ms; eta = 5, q = 0.5, 361 entries, 2.72 and 2.32;
-    // eta = 5, q = 0.6, 881 entries, 2.75 and 3.33)
+    // eta = 5, q = 0.6, 881 entries, 2.75 and 3.33.  d = 3 at degree 3, 125 entries
+    // and 28 products: launches 1 to 7% shorter in the form, batches 6% shorter to
+    // 3% longer, in FP32 at constant volatility)
     const CubicLayout lay(dp - 1, true, 1);
     if (live <= CubicLayout::groups(lay.rows) * lay.ka + CubicLayout::groups(lay.rows_t) * lay.kt)
         return 0;

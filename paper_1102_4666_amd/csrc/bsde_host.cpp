@@ -487,8 +487,7 @@ static void make_points(const bsde_problem_s *h, int k, std::vector<double> &pts
 }
 
 // Shapes of the set-up: the leading dimension of the n x pap point matrices
-// and the row chunks of the Gram kernel (about 2048 waves over the
-// 64 x 64 block pairs, at least 256 rows each)
+// and the row chunks of the Gram kernel
 static void setup_shape(int n, int pap, int &ld, int &rpc, int &chunks)
 {
     // an odd multiple of 64 rows: columns a power of two of rows apart would

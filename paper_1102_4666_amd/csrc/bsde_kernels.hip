@@ -76,11 +76,11 @@ __global__ __launch_bounds__(256) void project_kernel(
 
 constexpr int kMaxP = 512;
 
-// Entry e of the packed channel table (layout in bsde_common.h):
-// Gamma_e = sum_k vals[k] a[cols[k]], k in rowptr[e] .. rowptr[e+1]-1, with
-// a = alpha_in + beta; the sparse rows are those of the derivative channels
-// D_c alpha (channel 0, the first p entries, is a itself and also stores a
-// as the next coefficients).  FP64 and FP32 copies.
+// Entry e of the problem's table (the packed channels or the cubic form's rows,
+// layouts in bsde_common.h): Gamma_e = sum_k vals[k] a[cols[k]], k in rowptr[e]
+// .. rowptr[e+1]-1, with a = alpha_in + beta.  FP64 and FP32 copies.  The lanes of
+// the first p entries also store a as the next coefficients (a table has p
+// entries or more).
 __device__ __forceinline__ void channel_entries(
     const double *__restrict__ alpha_in, const double *__restrict__ beta, int segs,
     double *__restrict__ alpha_out, const int *__restrict__ rowptr,

@@ -1201,17 +1201,17 @@ __device__ __forceinline__ void run_tile(const PathParams &prm, uint64_t cbase,
     __syncthreads(); // red[] may be reused by the next tile
 }
 
-// Waves per SIMD the register allocation must allow.  The d = 10 (FP32)
-// and d = 5 (FP32 and FP64) kernels are held to three waves (168 registers
-// a lane): left to themselves those of d = 5 in FP64 and of d = 10 with the
-// channel table take 180-240 and run at two, and at three they run 10-17%
-// faster, with what does not fit (up to 340 bytes a lane) stored and reloaded
-// once per path, outside the Euler loop.  (In the cubic form FP32 takes 85 at
-// d = 5, five waves, and 149 to 168 at d = 10.)  At four waves (128
-// registers) the FP64 d = 5 kernel spills inside the Euler loop and takes 60%
-// longer, and the FP32 d = 10 one gains 2%.  d = 10 in FP64 runs at two
-// waves.  d = 2 in FP64 (eta = 5 wants over 256 registers) runs at two waves,
-// 29% faster than at one.
+// Waves per SIMD the register allocation must allow.  The d = 5 FP64 and the
+// d = 10 FP32 kernels are held to three waves (168 registers a lane): left to
+// themselves those of the channel form took 180-240 and ran at two, and at three
+// they ran 10-17% faster, with what does not fit (76 to 148 bytes a lane at d = 5
+// in FP64, up to 20 at d = 10) stored and reloaded once per path, outside the
+// Euler loop.  (FP32 takes 74 to 101 registers at d = 5, five waves, and 76 to 168
+// at d = 10.)  At four waves (128 registers) the FP64 d = 5 kernel spills inside
+// the Euler loop and takes 60% longer, and the FP32 d = 10 one gained 2%.  d = 10 in
+// FP64 runs at two waves, with up to 132 bytes a lane at degree 2 and 20 at degree
+// 3.  d = 2 in FP64 takes 105 to 142 registers, within the bound of two waves, and
+// runs at four or three.
 template <int D, typename Real>
 constexpr int min_waves()
 {

@@ -102,10 +102,12 @@ static void complete(bsde_server_s *S, Request *q, int status)
 }
 
 // Relative GPU cost of one Picard iteration of a problem: its path-steps
-// over the path-kernel rate of its dimension (path-steps/s measured on
-// MI355X with FP32 paths at the benchmark workloads; FP64 paths are 3-4x
-// slower).  Used only to group iterations into engine steps and problems
-// into the light and heavy lanes.
+// (those of points at T, which take none, included) over a path-kernel rate of
+// its dimension.  The rates are those the lanes' bound below was set with; at
+// the benchmark workloads the present kernels reach 1.6e12, 8.6e11, 3.7e11 and
+// 1.65e11 path-steps/s at d = 1, 2, 5 and 10 with FP32 paths, and 2.2 to 2.7 times
+// less in FP64.  Used only to group iterations into engine steps and problems into
+// the light and heavy lanes.
 static double iteration_cost(const bsde_problem_s *h)
 {
     double rate = h->d <= 1 ? 1.6e12 : h->d <= 2 ? 7e11 : h->d <= 3 ? 5e11
