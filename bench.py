@@ -188,14 +188,14 @@ ISSUE_CYCLES_D1_FP32 = {
 # hash is recorded with it and for the tiling it was taken at; otherwise
 # the line reports null.
 TRAFFIC = [
-    {"sources_sha16": "6dc45edbe372c17a", "tiling": [1, 4],
-     "fetch_kib": 11850.0, "write_kib": 246400.0,
+    {"sources_sha16": "2a98d69ddb8e868f", "tiling": [1, 4],
+     "fetch_kib": 11850.0, "write_kib": 249100.0,
      "profile": "profiles/path_kernel_d5_fp64_geo_basket_d5.md"},
-    {"sources_sha16": "6dc45edbe372c17a", "tiling": [4, 1],
-     "fetch_kib": 23370.0, "write_kib": 897500.0,
+    {"sources_sha16": "2a98d69ddb8e868f", "tiling": [4, 1],
+     "fetch_kib": 23370.0, "write_kib": 904000.0,
      "profile": "profiles/path_kernel_d5_fp64_geo_basket_d5.md"},
-    {"sources_sha16": "6dc45edbe372c17a", "tiling": [2, 2],
-     "fetch_kib": 15690.0, "write_kib": 478300.0,
+    {"sources_sha16": "2a98d69ddb8e868f", "tiling": [2, 2],
+     "fetch_kib": 15690.0, "write_kib": 483100.0,
      "profile": "profiles/path_kernel_d5_fp64_geo_basket_d5.md"},
 ]
 # Counter-derived figures of the same kernel (same profiles, same guard):
@@ -203,15 +203,15 @@ TRAFFIC = [
 # busy = SQ_VALU_MFMA_BUSY_CYCLES / 1024 SIMDs / cycles, FP64 vector FLOP
 # issued = 64 (2 FMA + MUL + ADD + TRANS) instructions per launch.
 COUNTERS = [
-    {"sources_sha16": "6dc45edbe372c17a", "tiling": [1, 4],
-     "valu_issue": 0.901, "mfma_busy": 0.0,
+    {"sources_sha16": "2a98d69ddb8e868f", "tiling": [1, 4],
+     "valu_issue": 0.903, "mfma_busy": 0.0,
      "fp64_vector_flop_per_launch": 5.04e11, "fp64_matrix_flop_per_launch": 0.0,
      "profile": "profiles/path_kernel_d5_fp64_geo_basket_d5.md"},
-    {"sources_sha16": "6dc45edbe372c17a", "tiling": [4, 1],
-     "valu_issue": 0.896, "mfma_busy": 0.0,
+    {"sources_sha16": "2a98d69ddb8e868f", "tiling": [4, 1],
+     "valu_issue": 0.895, "mfma_busy": 0.0,
      "fp64_vector_flop_per_launch": 5.11e11, "fp64_matrix_flop_per_launch": 0.0,
      "profile": "profiles/path_kernel_d5_fp64_geo_basket_d5.md"},
-    {"sources_sha16": "6dc45edbe372c17a", "tiling": [2, 2],
+    {"sources_sha16": "2a98d69ddb8e868f", "tiling": [2, 2],
      "valu_issue": 0.899, "mfma_busy": 0.0,
      "fp64_vector_flop_per_launch": 5.07e11, "fp64_matrix_flop_per_launch": 0.0,
      "profile": "profiles/path_kernel_d5_fp64_geo_basket_d5.md"},
